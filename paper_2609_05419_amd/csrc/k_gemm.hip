@@ -368,7 +368,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_i8_kernel(GemmArgs g) {
     int *claimed = reinterpret_cast<int *>(lds + kPipeBytes);
 
     const Wave w = wave_of(lds);
-    const int slots = g.chunk * g.batch;  // per XCD
+    const int slots = g.slots;  // per XCD
     // all arguments of the tile arithmetic and the first stage copies are
     // loaded here in one round, rather than in rounds behind each other
     asm volatile("" ::"s"(g.a), "s"(g.b), "s"(g.a_pstride), "s"(g.b_pstride), "s"(g.kblocks), "s"(g.mt),
@@ -377,7 +377,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_i8_kernel(GemmArgs g) {
     TileCoord tc;
     __amdgpu_buffer_rsrc_t rA, rB;
     if ((int)(blockIdx.x >> 3) < g.fixed) {
-        tc = tile_of(blockIdx.x & 7, blockIdx.x >> 3, g.mt, g.nt, g.chunk, g.deal);
+        tc = tile_of(blockIdx.x & 7, blockIdx.x >> 3, g.mt, g.nt, g.chunk, g.deal, g.batch);
         if (!tc.valid) return;  // whole workgroup: no barrier is pending
     } else {
         if (w.wave == 0) {
@@ -387,7 +387,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_i8_kernel(GemmArgs g) {
         __syncthreads();
         const int c = *claimed;
         if (c < 0) return;  // whole workgroup: no barrier is pending
-        tc = tile_of(c >> kSlotBits, c & ((1 << kSlotBits) - 1), g.mt, g.nt, g.chunk, g.deal);
+        tc = tile_of(c >> kSlotBits, c & ((1 << kSlotBits) - 1), g.mt, g.nt, g.chunk, g.deal, g.batch);
         if (!tc.valid) return;
     }
     rA = rsrc_a(g, tc);
@@ -431,12 +431,13 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_i8_kernel(GemmArgs g) {
 hipError_t launch_gemm(const GemmArgs &ga_in, hipStream_t st) {
     static_assert(kThreads * 16 * kLoadsPerStage == 2 * kStageBytes, "stage copy covers A and B");
     GemmArgs ga = ga_in;
-    const GemmSchedule sc = gemm_schedule(ga.mt, ga.nt, ga.kblocks, ga.batch, kStageBytes);
+    const GemmSchedule sc = gemm_plan(ga.mt, ga.nt, ga.kblocks, ga.batch, kStageBytes);
     if (sc.grid == 0) return hipSuccess;
     if (sc.grid > 0x7FFFFFFF || sc.slots >= (1L << kSlotBits)) return hipErrorInvalidValue;
     ga.deal = sc.deal;
     ga.chunk = sc.chunk;
     ga.fixed = (int)sc.fixed;
+    ga.slots = (int)sc.slots;
     const long grid = sc.grid;
     gemm_i8_kernel<<<(unsigned)grid, kThreads, 0, st>>>(ga);
     return hipGetLastError();

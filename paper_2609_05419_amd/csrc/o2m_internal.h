@@ -208,8 +208,8 @@ struct GemmArgs {
     int mt, nt, kblocks;                     // tiles along m, n; k stages
     int batch;
     int ldc;
-    int chunk;                               // tiles per XCD per product (set by the launcher)
-    int deal;                                // 1: 32-tile windows dealt round-robin to the XCDs
+    int chunk, deal;                         // tile order (tile_schedule.h; set by the launcher)
+    int slots;                               // slots per XCD (launcher)
     int fixed;                               // slots per XCD taken by workgroup index (launcher)
     unsigned *queue;                         // 8 pool counters, one per XCD, kQueueStride
                                              // apart; zero at launch

@@ -30,6 +30,21 @@
 // which start at zero), and every one is claimed: a workgroup only finds all
 // pools empty when all their slots are taken, and the pools have more
 // workgroups than slots.
+//
+// Products of fewer than 8 windows (256 tiles) would give an XCD less than one
+// window of each, so with a share of every product on every XCD the 32 tiles
+// resident there would come from several products and share few stages
+// (2 of 16 tiles of a 1024 x 1024 product: 3 operand strips for 2 tiles).
+// Those launches are laid out spread instead (gemm_plan): the tiles of all
+// products form one sequence, product-major and in the grouped order, and
+// each XCD takes one contiguous eighth of it, so that its resident tiles are
+// neighbours of one or two products (16 tiles for 8 strips) and every operand
+// strip is fetched by one or two XCDs only.  GEMM phase, N = 16, before ->
+// after: 1024^3 55 -> 43 us, 2048^3 249 -> 236, 1024 x 1024 x 65536 1702 -> 1448,
+// 500 x 333 x 777 26 -> 21; level at 144 and 256 tiles.  A single tile-row or
+// tile-column has no such neighbours (its long operand is read once either
+// way) and stays product-major while it fills the XCDs: 4096 x 96 x 4096 took
+// 132 us spread against 130.
 #pragma once
 
 #ifndef O2M_HD
@@ -43,19 +58,30 @@ constexpr int kGroupRows = 8;     // tile-rows per group of the grouped order
 constexpr int kWindowTiles = 32;  // tiles per window (8 tile-rows x 4 tile-columns)
 constexpr int kSlotBits = 28;     // a claimed slot travels as x << 28 | slot
 
+constexpr int kSpread = 2;        // `deal` of a launch laid out spread
+
 struct TileCoord {
     int p, ti, tj;
     bool valid;
 };
 
 // Slot `slot` of XCD x's queue -> product p, tile (ti, tj), or an idle slot.
-O2M_HD inline TileCoord tile_of(int x, int slot, int mt, int nt, int chunk, int deal) {
+// deal 0: contiguous chunks of each product, 1: windows dealt round-robin,
+// kSpread: slots x chunk + slot of the sequence of all `batch` products' tiles.
+O2M_HD inline TileCoord tile_of(int x, int slot, int mt, int nt, int chunk, int deal, int batch = 0) {
     TileCoord c;
-    c.p = slot / chunk;
-    const int s = slot - c.p * chunk;  // the slot within the product
-    const int t = deal ? (kXcds * (s / kWindowTiles) + x) * kWindowTiles + s % kWindowTiles
-                       : x * chunk + s;  // index in the grouped order
-    c.valid = t < mt * nt;
+    int t;  // index in the grouped order of the product
+    if (deal == kSpread) {
+        const int g = x * chunk + slot;
+        c.p = g / (mt * nt);
+        t = g - c.p * (mt * nt);
+        c.valid = c.p < batch;
+    } else {
+        c.p = slot / chunk;
+        const int s = slot - c.p * chunk;  // the slot within the product
+        t = deal ? (kXcds * (s / kWindowTiles) + x) * kWindowTiles + s % kWindowTiles : x * chunk + s;
+        c.valid = t < mt * nt;
+    }
     c.ti = c.tj = 0;
     if (!c.valid) return c;  // idle slot (its group arithmetic would divide by zero)
     const int group = t / (kGroupRows * nt);
@@ -69,12 +95,21 @@ O2M_HD inline TileCoord tile_of(int x, int slot, int mt, int nt, int chunk, int 
 
 // Launch parameters of one batched int8 GEMM.
 struct GemmSchedule {
-    int deal;    // 1: windows dealt round-robin to the XCDs
-    int chunk;   // slots per XCD and product
+    int deal;    // 1: windows dealt round-robin to the XCDs, kSpread: spread
+    int chunk;   // slots per XCD and product (spread: per XCD)
     long slots;  // slots per XCD over the batch
     long fixed;  // of those, taken by workgroup index; the rest are pooled
     long grid;   // workgroups: kXcds * slots plus the spares (0 when nothing to do)
 };
+
+// Splits s.slots into fixed and pooled ones and sets the grid: pooled are the
+// last 1/8 of each XCD's slots, plus one spare workgroup per 12 slots, so that
+// a faster XCD can take slots of a slower one's pool.
+O2M_HD inline void pool_slots(GemmSchedule &s, int kblocks) {
+    const bool pool = kblocks >= 128 && s.slots >= 256;
+    s.fixed = pool ? s.slots - s.slots / 8 : s.slots;
+    s.grid = kXcds * (s.slots + (pool ? (s.slots + 11) / 12 : 0));
+}
 
 // mt x nt tiles per product, kblocks k-stages of stage_bytes per operand
 // tile, batch products.  grid stays 0 for an empty problem; the caller
@@ -90,11 +125,20 @@ O2M_HD inline GemmSchedule gemm_schedule(int mt, int nt, int kblocks, int batch,
     s.deal = windows >= 2 * kXcds && plane_bytes > (256L << 20) ? 1 : 0;
     s.chunk = (int)(s.deal ? kWindowTiles * ((windows + kXcds - 1) / kXcds) : (tiles + kXcds - 1) / kXcds);
     s.slots = (long)s.chunk * batch;
-    // pooled: the last 1/8 of each XCD's slots, plus one spare workgroup per
-    // 12 slots, so that a faster XCD can take slots of a slower one's pool
-    const bool pool = kblocks >= 128 && s.slots >= 256;
-    s.fixed = pool ? s.slots - s.slots / 8 : s.slots;
-    s.grid = kXcds * (s.slots + (pool ? (s.slots + 11) / 12 : 0));
+    pool_slots(s, kblocks);
+    return s;
+}
+
+// The schedule a launch uses: spread below 8 windows per product (a single
+// tile-row or tile-column: below one tile per XCD), otherwise gemm_schedule.
+O2M_HD inline GemmSchedule gemm_plan(int mt, int nt, int kblocks, int batch, long stage_bytes) {
+    const long tiles = (long)mt * nt;
+    if (tiles <= 0 || batch <= 0 || kblocks <= 0 || tiles >= (mt > 1 && nt > 1 ? kXcds * kWindowTiles : kXcds))
+        return gemm_schedule(mt, nt, kblocks, batch, stage_bytes);
+    GemmSchedule s = {kSpread, 0, 0, 0, 0};
+    s.slots = (tiles * batch + kXcds - 1) / kXcds;
+    s.chunk = (int)s.slots;
+    pool_slots(s, kblocks);
     return s;
 }
 
