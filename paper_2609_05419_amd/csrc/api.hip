@@ -385,22 +385,18 @@ o2m_status run(const Call &c) {
     // one GEMM per modulus gives C+ = A+ B-^T + B+ A-^T (Section 5, HER2K).
     const int kb = g.kblocks;
     const int pkb = g.halves * kb;
-    const int rmode = is_real_split(c.op) ? 2 : amode;
-    const int khalf = is_real_split(c.op) ? kc : 0;
-    const int32_t *Eq = c.op == kOpG ? nullptr : b.E;
-    PlaneGeom ga = {c.m, kc, c.k, g.a_pad, kb, pkb, 0, two ? kb : 0, g.plane_a, c.ta == 'C'};
-    O2M_TRY(launch_residues(rmode, et, c.A, c.lda, Eq, pA, digits(c.scaling, pA), khalf, ga, t->res,
-                            b.planes_a, c.st));
-    if (two) {
-        PlaneGeom gb2 = {c.m, kc, c.k, g.a_pad, kb, pkb, kb, 0, g.plane_a};
-        O2M_TRY(launch_residues(rmode, et, c.B, c.ldb, Eq, pA, digits(c.scaling, pA), khalf, gb2, t->res,
-                                b.planes_a, c.st));
-    }
-    if (!sym) {
-        PlaneGeom gb = {c.n, c.k, c.k, g.b_pad, kb, kb, 0, 0, g.plane_b, c.tb == 'C'};
-        O2M_TRY(launch_residues(bmode, et, c.B, c.ldb, c.op == kOpG ? nullptr : b.F, pB, digits(c.scaling, pB), 0,
-                                gb, t->res, b.planes_b, c.st));
-    }
+    const bool split = is_real_split(c.op);
+    ResidueSource src[2];
+    memset(src, 0, sizeof src);
+    src[0] = {c.A, c.lda, amode, b.E, pA, digits(c.scaling, pA), split ? kc : 0,
+              {c.m, kc, c.k, g.a_pad, kb, pkb, 0, two ? kb : 0, g.plane_a, c.ta == 'C'}, b.planes_a};
+    if (two)
+        src[1] = {c.B, c.ldb, amode, b.E, pA, digits(c.scaling, pA), split ? kc : 0,
+                  {c.m, kc, c.k, g.a_pad, kb, pkb, kb, 0, g.plane_a, 0}, b.planes_a};
+    else if (!sym)
+        src[1] = {c.B, c.ldb, bmode, b.F, pB, digits(c.scaling, pB), 0,
+                  {c.n, c.k, c.k, g.b_pad, kb, kb, 0, 0, g.plane_b, c.tb == 'C'}, b.planes_b};
+    O2M_TRY(launch_residues(et, split, two || !sym ? 2 : 1, src, t->res, c.st));
     phase_mark(slot, 2, c.st);
 
     // ---- K3: int8 GEMMs ----------------------------------------------------

@@ -28,6 +28,7 @@
 // 16 read + 2N written (8 + 2N for fp32 input).
 #include "o2m_internal.h"
 
+#include <string.h>
 #include <type_traits>
 
 namespace o2m {
@@ -92,6 +93,15 @@ __device__ inline uint32_t pack4(uint32_t b0, uint32_t b1, uint32_t b2, uint32_t
 // one wave per SIMD; a fragment then goes to two waves, 32 chunks each.
 template <int D> constexpr int per_thread() { return D >= 4 ? 8 : 16; }
 
+// The split of the moduli (mchunk): waves that a launch is brought to, and
+// moduli that a wave keeps at least.  2048 waves are two per SIMD; below, the
+// serial chain of a wave is what takes the time (500 x 333 x 777, 896 waves:
+// residue phase 17.9 us whole, 15.7 in two parts, 18 in eight), above, the
+// entries read again cost more than the split gives (1024^3, 2048 waves: 24.8
+// us whole, 26.1 in two parts, 31.5 in four).
+constexpr long kResidueWaves = 2048;
+constexpr int kMinModuli = 2;
+
 // PT residue bytes of one lane, contiguous in the plane (16- or 8-byte store).
 // The stores are non-temporal (no cache allocation): the planes are far
 // larger than the caches and are read back only by the GEMM, from its own
@@ -109,33 +119,63 @@ __device__ inline void store_words(int8_t *dst, const uint32_t (&w)[PT / 4]) {
     }
 }
 
-// MODE 0: rows of X (A, column-major m x k): entry (r, kk) at X[r + kk*ld]
-// MODE 1: columns of X (B, column-major k x n): entry (r, kk) at X[kk + r*ld]
-// MODE 2: SYRK, X real column-major n x k: (r, kk) = X[r + kk ld] + i X[r + (kk+kh) ld]
-// conj: the operand is the complex conjugate of X (imaginary parts negated)
+// One launch takes up to two sources (the A and the B operand of a GEMM, the
+// two matrices of a rank-2k update): its workgroups are the first source's,
+// then the second's.  Two launches left the chip draining twice: residue phase
+// at N = 16, two launches -> one, 1024^3 37 -> 25 us, 2048^3 88 -> 76 us,
+// 96 x 80 x 200 33 -> 9 us (there mostly the loads at the edges, which went out
+// one at a time, and the split of the moduli), 8192^3 level.  Per source (ResidueSource, o2m_internal.h):
+//   rows (mode 0): operand rows are rows of X, entry (r, kk) at X[r + kk*ld]
+//   columns (mode 1): operand rows are columns of X, (r, kk) at X[kk + r*ld]
+//   SPLIT (SYRK, rows only): X real, (r, kk) = X[r + kk ld] + i X[r + (kk+kh) ld]
+//   conj: the operand is the complex conjugate of X (imaginary parts negated)
 // D: base-2^26 digits of the quantized values (1..5, from their bound)
 // PAIRS (complex fp32, the host sets it when every pair is 16-byte aligned):
-// MODE 1 reads two consecutive entries of a column of B per 16-byte load;
-// MODE 0 reads rows 2i, 2i + 1 of a column of A per 16-byte load, the even
-// lane of a lane pair columns kk0..kk0+7 and the odd lane kk0+8..kk0+15, and
-// the pair then swaps halves so that each lane holds its own row's 16 entries
-template <int MODE, ElemType ET, int D, bool SCALED, bool PAIRS = false>
-__global__ __launch_bounds__(256, D == 1 ? 3 : 1) void residue_kernel(const void *X, int ld, const int32_t *E,
-                                                      int shift, int khalf, int kreal, int rows, int k,
-                                                      int rows_pad, int kblocks, int plane_kblocks,
-                                                      int kofs_p, int kofs_m, size_t plane_bytes,
-                                                      int conj, ResidueParams rp, int8_t *planes) {
+// columns read two consecutive entries per 16-byte load; rows read rows 2i,
+// 2i + 1 of a column per 16-byte load, the even lane of a lane pair columns
+// kk0..kk0+7 and the odd lane kk0+8..kk0+15, and the pair then swaps halves so
+// that each lane holds its own row's 16 entries
+//
+// Workgroup row blockIdx.y computes the moduli [y mchunk, (y + 1) mchunk): a
+// wave's 2N residues per entry are a serial chain of ~100 instructions per
+// entry, so an operand of few fragments left most of the chip idle behind
+// them (1024 x 1024: one wave per SIMD).  Splitting the moduli re-reads the
+// entries, from the caches at those sizes (launch_residues).
+struct ResidueArgs {
+    ResidueSource src[2];
+    unsigned blocks0;        // workgroups of src[0]
+    int mchunk;
+    ResidueParams rp;
+};
+
+template <ElemType ET, int D, bool SCALED, bool PAIRS, bool SPLIT>
+__global__ __launch_bounds__(256, D == 1 ? 3 : 1) void residue_kernel(ResidueArgs a) {
     constexpr int PT = per_thread<D>();
     constexpr int kHalves = 16 / PT;                          // waves per fragment
+    const ResidueParams &rp = a.rp;
+    // what the loads need is read of both sources at once and then selected:
+    // a read of the selected source would wait for the selection first
+    const ResidueSource &s0 = a.src[0], &s1 = a.src[1];
+    asm volatile("" ::"s"(a.blocks0), "s"(s0.X), "s"(s1.X), "s"(s0.E), "s"(s1.E), "s"(s0.ld), "s"(s1.ld),
+                 "s"(s0.g.rows), "s"(s1.g.rows), "s"(s0.g.k), "s"(s1.g.k), "s"(s0.g.rows_pad), "s"(s1.g.rows_pad),
+                 "s"(s0.g.kblocks), "s"(s1.g.kblocks), "s"(s0.mode), "s"(s1.mode));
+    const bool second = blockIdx.x >= a.blocks0;
+    const ResidueSource &o = second ? s1 : s0;   // what is used later
+    const unsigned block = blockIdx.x - (second ? a.blocks0 : 0u);
+    const bool cols = !SPLIT && (second ? s1.mode : s0.mode) == 1;
+    const void *X = second ? s1.X : s0.X;
+    const int32_t *E = second ? s1.E : s0.E;
+    const int rows = second ? s1.g.rows : s0.g.rows, k = second ? s1.g.k : s0.g.k, ld = second ? s1.ld : s0.ld;
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));  // wave-uniform
+    const int wave = __builtin_amdgcn_readfirstlane(block * 4 + (threadIdx.x >> 6));  // wave-uniform
     const int frag = wave / kHalves, half = wave % kHalves;   // one fragment per kHalves waves
-    const int frows = rows_pad / kFragRows;                   // fragments along rows
-    const int fks = kblocks;                                  // fragments along k
-    int fr, fk;
+    const int frows = (second ? s1.g.rows_pad : s0.g.rows_pad) / kFragRows;  // fragments along rows
+    const int fks = second ? s1.g.kblocks : s0.g.kblocks;                    // fragments along k
     if (frag >= frows * fks) return;
-    if (MODE == 1) { fk = frag % fks; fr = frag / fks; }      // B: walk k fastest (contiguous)
-    else { fr = frag % frows; fk = frag / frows; }            // A: walk rows fastest
+    // columns: walk k fastest (contiguous); rows: walk rows fastest
+    const int per = cols ? fks : frows;
+    const int hi = frag / per, lo = frag - hi * per;
+    const int fk = cols ? lo : hi, fr = cols ? hi : lo;
     // the fragment's 16-byte lane chunk and the part of it this lane fills;
     // with two waves per fragment each takes 32 whole chunks (adjacent lanes
     // fill the two halves of one), so that a store covers 512 contiguous bytes
@@ -145,16 +185,17 @@ __global__ __launch_bounds__(256, D == 1 ? 3 : 1) void residue_kernel(const void
     const int kk0 = fk * kStageK + (chunk >> 4) * 16 + part * PT;
 
     // ---- load and quantize (step 3) -------------------------------------
-    // A wave whose fragment (16 rows x 64 k) lies inside the operand takes
-    // every load unguarded, so all of them are in flight before the first is
-    // used; the guarded form is taken at the edges only.  (With a per-lane
-    // guard around each load the compiler moves the quantization of the value
-    // into the guarded branch, where it must wait for that load: the loads
-    // then went out one at a time.)
+    // Every load is taken unguarded, so that all of them are in flight before
+    // the first is used.  (With a per-lane guard around each load the compiler
+    // moves the quantization of the value into the guarded branch, where it
+    // must wait for that load: the loads then go out one at a time.)  A wave
+    // whose fragment (16 rows x 64 k) lies inside the operand reads it as it
+    // is; at the edges the indices are clamped into the operand and the values
+    // beyond it dropped.
     typedef typename Digit<D>::type DT;
     DT xr[D][PT], xi[D][PT];
     const bool inner = fr * kFragRows + kFragRows <= rows && fk * kStageK + kStageK <= k &&
-                       (MODE != 2 || fk * kStageK + kStageK + khalf <= kreal);
+                       (!SPLIT || fk * kStageK + kStageK + o.khalf <= o.g.kreal);
     // the row's exponent is fetched first and used once the entries' loads
     // are issued (every padded row has an entry)
     int erow = 0;
@@ -164,12 +205,12 @@ __global__ __launch_bounds__(256, D == 1 ? 3 : 1) void residue_kernel(const void
     auto settle = [&]() {
         if constexpr (SCALED) {
             live = live && erow != INT32_MIN;  // non-finite row: output masked later
-            sh = shift - erow;
+            sh = o.shift - erow;
         }
     };
     auto put = [&](int e, double vr, double vi) {
         if (!live) vr = vi = 0.0;
-        if (conj) vi = -vi;                  // conjugated operand: exact
+        if (o.g.conj) vi = -vi;              // conjugated operand: exact
         if (SCALED) {
             vr = rint(ldexp(vr, sh));
             vi = rint(ldexp(vi, sh));
@@ -177,30 +218,53 @@ __global__ __launch_bounds__(256, D == 1 ? 3 : 1) void residue_kernel(const void
         split_digits<D, PT>(vr, xr, e);
         split_digits<D, PT>(vi, xi, e);
     };
-    auto load_all = [&](auto edge) {
-        constexpr bool EDGE = decltype(edge)::value;
-        if constexpr (PAIRS && MODE == 0) {
-            static_assert(ET == kF32 && PT == 16, "pairs of complex fp32 rows, one lane chunk per lane");
+    auto load_single = [&](auto edge, auto columns) {
+        constexpr bool EDGE = decltype(edge)::value, COLS = decltype(columns)::value;
+        // entry (rc, kc) at index base + kc ks
+        const int rc = EDGE ? min(r, rows - 1) : r;
+        const size_t ks = COLS ? 1 : (size_t)ld;
+        const size_t base = COLS ? (size_t)rc * ld : (size_t)rc;
+        const size_t first = base + kk0 * ks;
+        double vr[PT], vi[PT];
+#pragma unroll
+        for (int e = 0; e < PT; ++e) {
+            const size_t at = EDGE ? base + min(kk0 + e, k - 1) * ks : first + e * ks;
+            if constexpr (!SPLIT) {
+                const double2 v = Load<ET>::get(X, at);
+                vr[e] = v.x; vi[e] = v.y;
+            } else {
+                const double *Xr = reinterpret_cast<const double *>(X);
+                vr[e] = Xr[at];
+                vi[e] = Xr[EDGE ? base + min(kk0 + e + o.khalf, o.g.kreal - 1) * ks : at + o.khalf * ks];
+            }
+        }
+        settle();
+#pragma unroll
+        for (int e = 0; e < PT; ++e) {
+            if (EDGE && kk0 + e >= k) vr[e] = vi[e] = 0.0;
+            if (EDGE && SPLIT && kk0 + e + o.khalf >= o.g.kreal) vi[e] = 0.0;
+            put(e, vr[e], vi[e]);
+        }
+    };
+    auto load_pairs = [&]() {
+        const float2 *Xf = reinterpret_cast<const float2 *>(X);
+        if (cols) {
+            const float2 *Xc = Xf + (size_t)r * ld + kk0;
+            float4 v[PT / 2];
+#pragma unroll
+            for (int e = 0; e < PT / 2; ++e) v[e] = *reinterpret_cast<const float4 *>(Xc + 2 * e);
+            settle();
+#pragma unroll
+            for (int e = 0; e < PT / 2; ++e) {
+                put(2 * e, (double)v[e].x, (double)v[e].y);
+                put(2 * e + 1, (double)v[e].z, (double)v[e].w);
+            }
+        } else if constexpr (PT == 16) {   // (the host pairs rows up to three digits)
             const bool odd = lane & 1;
-            const int re = r - (int)odd;                 // the pair's even row
-            const float2 *Xa = reinterpret_cast<const float2 *>(X);
+            const float2 *Xa = Xf + (r - (int)odd) + (size_t)(kk0 + (odd ? 8 : 0)) * ld;   // the pair's even row
             float4 v[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int kk = kk0 + (odd ? 8 : 0) + j;
-                v[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                if (!EDGE) {
-                    v[j] = *reinterpret_cast<const float4 *>(Xa + (size_t)re + (size_t)kk * ld);
-                } else if (kk < k) {
-                    if (re + 1 < rows) {
-                        v[j] = *reinterpret_cast<const float4 *>(Xa + (size_t)re + (size_t)kk * ld);
-                    } else if (re < rows) {
-                        const float2 t = Xa[(size_t)re + (size_t)kk * ld];
-                        v[j].x = t.x;
-                        v[j].y = t.y;
-                    }
-                }
-            }
+            for (int j = 0; j < 8; ++j) v[j] = *reinterpret_cast<const float4 *>(Xa + (size_t)j * ld);
             settle();
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
@@ -210,63 +274,38 @@ __global__ __launch_bounds__(256, D == 1 ? 3 : 1) void residue_kernel(const void
                 put(j, odd ? rx : v[j].x, odd ? ry : v[j].y);
                 put(8 + j, odd ? v[j].z : rx, odd ? v[j].w : ry);
             }
-        } else if constexpr (PAIRS) {
-            static_assert(MODE == 1 && ET == kF32, "pairs of complex fp32 entries along a column");
-            const float2 *Xc = reinterpret_cast<const float2 *>(X) + (size_t)r * ld;
-            float4 v[PT / 2];
-#pragma unroll
-            for (int e = 0; e < PT; e += 2) {
-                const int kk = kk0 + e;
-                v[e / 2] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                if (!EDGE) {
-                    v[e / 2] = *reinterpret_cast<const float4 *>(Xc + kk);
-                } else if (live && kk + 1 < k) {
-                    v[e / 2] = *reinterpret_cast<const float4 *>(Xc + kk);
-                } else if (live && kk < k) {
-                    const float2 t = Xc[kk];
-                    v[e / 2].x = t.x;
-                    v[e / 2].y = t.y;
-                }
-            }
-            settle();
-#pragma unroll
-            for (int e = 0; e < PT; e += 2) {
-                put(e, (double)v[e / 2].x, (double)v[e / 2].y);
-                put(e + 1, (double)v[e / 2].z, (double)v[e / 2].w);
-            }
-        } else {
-            double vr[PT], vi[PT];
-#pragma unroll
-            for (int e = 0; e < PT; ++e) {
-                const int kk = kk0 + e;
-                vr[e] = 0.0;
-                vi[e] = 0.0;
-                if (!EDGE || (live && kk < k)) {
-                    if (MODE == 0) {
-                        const double2 v = Load<ET>::get(X, (size_t)r + (size_t)kk * ld);
-                        vr[e] = v.x; vi[e] = v.y;
-                    } else if (MODE == 1) {
-                        const double2 v = Load<ET>::get(X, (size_t)kk + (size_t)r * ld);
-                        vr[e] = v.x; vi[e] = v.y;
-                    } else {
-                        const double *Xr = reinterpret_cast<const double *>(X);
-                        vr[e] = Xr[(size_t)r + (size_t)kk * ld];
-                        if (!EDGE || kk + khalf < kreal) vi[e] = Xr[(size_t)r + (size_t)(kk + khalf) * ld];
-                    }
-                }
-            }
-            settle();
-#pragma unroll
-            for (int e = 0; e < PT; ++e) put(e, vr[e], vi[e]);
         }
     };
-    if (__builtin_expect(inner, 1)) load_all(std::false_type());
-    else load_all(std::true_type());
+    // a fragment of padding only has nothing to read: zero residues
+    const bool padding = fr * kFragRows >= rows || fk * kStageK >= k;
+    if (__builtin_expect(inner, 1)) {
+        if constexpr (PAIRS) load_pairs();
+        else if (!SPLIT && cols) load_single(std::false_type(), std::true_type());
+        else load_single(std::false_type(), std::false_type());
+    } else if (!padding) {
+        if (!SPLIT && cols) load_single(std::true_type(), std::true_type());
+        else load_single(std::true_type(), std::false_type());
+    }
+
+    const size_t plane_bytes = o.g.plane_bytes;
+    int8_t *dst_p = o.planes + plane_offset(r, kk0 + o.g.kofs_p * kStageK, o.g.plane_kblocks);
+    int8_t *dst_m = o.planes + plane_offset(r, kk0 + o.g.kofs_m * kStageK, o.g.plane_kblocks) + plane_bytes;
+    const int l0 = blockIdx.y * a.mchunk, l1 = min(rp.n, l0 + a.mchunk);
+    const int l2m = min(rp.n2, l1), l3m = max(rp.n2, l0);   // 2M moduli [l0, l2m), 3M [l3m, l1)
+    if (padding) {
+        const uint32_t z[PT / 4] = {};
+        for (int l = l0; l < l2m; ++l) {
+            store_words<PT>(dst_p + (size_t)(2 * l) * plane_bytes, z);
+            store_words<PT>(dst_m + (size_t)(2 * l) * plane_bytes, z);
+        }
+        for (int l = l3m; l < l1; ++l)
+            for (int c = 0; c < 3; ++c)
+                store_words<PT>(dst_p + (size_t)(2 * rp.n2 + 3 * (l - rp.n2) + c) * plane_bytes, z);
+        return;
+    }
 
     // ---- residues and 2M pre per modulus (step 4, eq. 2m-pre) -------------
-    int8_t *dst_p = planes + plane_offset(r, kk0 + kofs_p * kStageK, plane_kblocks);
-    int8_t *dst_m = planes + plane_offset(r, kk0 + kofs_m * kStageK, plane_kblocks) + plane_bytes;
-    for (int l = 0; l < rp.n2; ++l) {
+    for (int l = l0; l < l2m; ++l) {
         const double inv = rp.inv[l];
         const double s = (double)rp.root[l];
         const uint32_t negm = (uint32_t)(-rp.mod[l]) & 0xFFFFFFu;
@@ -297,7 +336,7 @@ __global__ __launch_bounds__(256, D == 1 ? 3 : 1) void residue_kernel(const void
     }
 
     // ---- hybrid sets: residues of Xr, Xi and Xr + Xi for 3M (Section 3.2) ---
-    for (int l = rp.n2; l < rp.n; ++l) {
+    for (int l = l3m; l < l1; ++l) {
         const double inv = rp.inv[l];
         const uint32_t negm = (uint32_t)(-rp.mod[l]) & 0xFFFFFFu;
         uint32_t w[3][PT / 4];
@@ -332,50 +371,55 @@ __global__ __launch_bounds__(256, D == 1 ? 3 : 1) void residue_kernel(const void
 
 }  // namespace
 
-hipError_t launch_residues(int mode, ElemType et, const void *X, int ld, const int32_t *E, int shift,
-                           int digits, int khalf, const PlaneGeom &g, const ResidueParams &rp,
-                           int8_t *planes, hipStream_t st) {
-    const int kreal = khalf > 0 ? g.kreal : 0;
-    // waves: one per fragment, two for four and five digits (per_thread)
-    const long frags = (long)(g.rows_pad / kFragRows) * (long)g.kblocks;
-    const long waves = frags * (digits >= 4 ? 2 : 1);
-    if ((waves + 3) / 4 > 0x7FFFFFFF) return hipErrorInvalidValue;
-    const unsigned blocks = (unsigned)((waves + 3) / 4);
+static bool pairs_of(ElemType et, const ResidueSource &s) {
     // complex fp32 entries in 16-byte pairs when every pair is aligned: along
-    // a column of B (k-chunks start at even k) or across rows 2i, 2i + 1 of A
-    // (lane chunks of one row, up to three digits); an even ld and a 16-byte
-    // aligned base suffice
-    const bool pairs = et == kF32 && (mode == 1 || digits <= 3) && ld % 2 == 0 && ((uintptr_t)X & 15) == 0;
-#define O2M_RES(M, T, DD, SC, PR)                                                                \
-    residue_kernel<M, T, DD, SC, PR><<<blocks, 256, 0, st>>>(X, ld, E, shift, khalf, kreal, g.rows, g.k, \
-                                                            g.rows_pad, g.kblocks, g.plane_kblocks, \
-                                                            g.kofs_p, g.kofs_m, g.plane_bytes, g.conj, rp, \
-                                                            planes)
-#define O2M_RES_D(M, T, PR)                                   \
-    switch (digits) {                                         \
-    case 1: O2M_RES(M, T, 1, true, PR); break;                \
-    case 2: O2M_RES(M, T, 2, true, PR); break;                \
-    case 3: O2M_RES(M, T, 3, true, PR); break;                \
-    case 4: O2M_RES(M, T, 4, true, PR); break;                \
-    case 5: O2M_RES(M, T, 5, true, PR); break;                \
-    default: return hipErrorInvalidValue;                     \
+    // a column (k-chunks start at even k) or across rows 2i, 2i + 1 (lane
+    // chunks of one row, up to three digits); an even ld and a 16-byte aligned
+    // base suffice
+    return et == kF32 && (s.mode == 1 || s.digits <= 3) && s.ld % 2 == 0 && ((uintptr_t)s.X & 15) == 0;
+}
+
+hipError_t launch_residues(ElemType et, bool split, int count, const ResidueSource *src, const ResidueParams &rp,
+                           hipStream_t st) {
+    if (count < 1 || count > 2) return hipErrorInvalidValue;
+    const int digits = src[0].digits;
+    const bool pairs = pairs_of(et, src[0]);
+    if (count == 2 && (src[1].digits != digits || pairs_of(et, src[1]) != pairs)) {
+        const hipError_t e = launch_residues(et, split, 1, src, rp, st);
+        return e != hipSuccess ? e : launch_residues(et, split, 1, src + 1, rp, st);
     }
-    if (mode == 0 && et == kF64) { O2M_RES_D(0, kF64, false) }
-    else if (mode == 1 && et == kF64) { O2M_RES_D(1, kF64, false) }
-    else if (mode == 0 && et == kF32 && pairs) {
-        switch (digits) {
-        case 1: O2M_RES(0, kF32, 1, true, true); break;
-        case 2: O2M_RES(0, kF32, 2, true, true); break;
-        case 3: O2M_RES(0, kF32, 3, true, true); break;
-        default: return hipErrorInvalidValue;
-        }
+    // waves: one per fragment, two for four and five digits (per_thread)
+    long waves[2] = {0, 0};
+    for (int i = 0; i < count; ++i)
+        waves[i] = (long)(src[i].g.rows_pad / kFragRows) * (long)src[i].g.kblocks * (digits >= 4 ? 2 : 1);
+    const long blocks = (waves[0] + 3) / 4 + (waves[1] + 3) / 4;
+    if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
+    ResidueArgs a;
+    memset(&a, 0, sizeof a);
+    for (int i = 0; i < count; ++i) a.src[i] = src[i];
+    a.blocks0 = (unsigned)((waves[0] + 3) / 4);
+    // moduli per workgroup: split until the launch has kResidueWaves waves
+    a.mchunk = rp.n;
+    while (a.mchunk > kMinModuli && blocks * 4 * ((rp.n + a.mchunk - 1) / a.mchunk) < kResidueWaves)
+        a.mchunk = (a.mchunk + 1) / 2;
+    a.rp = rp;
+    const dim3 grid((unsigned)blocks, (unsigned)((rp.n + a.mchunk - 1) / a.mchunk));
+#define O2M_RES(T, DD, SC, PR, SP) residue_kernel<T, DD, SC, PR, SP><<<grid, 256, 0, st>>>(a)
+#define O2M_RES_D(T, PR, SP)                               \
+    switch (digits) {                                      \
+    case 1: O2M_RES(T, 1, true, PR, SP); break;            \
+    case 2: O2M_RES(T, 2, true, PR, SP); break;            \
+    case 3: O2M_RES(T, 3, true, PR, SP); break;            \
+    case 4: O2M_RES(T, 4, true, PR, SP); break;            \
+    case 5: O2M_RES(T, 5, true, PR, SP); break;            \
+    default: return hipErrorInvalidValue;                  \
     }
-    else if (mode == 0 && et == kF32) { O2M_RES_D(0, kF32, false) }
-    else if (mode == 1 && et == kF32 && pairs) { O2M_RES_D(1, kF32, true) }
-    else if (mode == 1 && et == kF32) { O2M_RES_D(1, kF32, false) }
-    else if (mode == 2 && et == kR64) { O2M_RES_D(2, kR64, false) }
-    else if (mode == 0 && et == kI32) O2M_RES(0, kI32, 2, false, false);
-    else if (mode == 1 && et == kI32) O2M_RES(1, kI32, 2, false, false);
+    if (split && et == kR64) { O2M_RES_D(kR64, false, true) }
+    else if (split) return hipErrorInvalidValue;
+    else if (et == kF64) { O2M_RES_D(kF64, false, false) }
+    else if (et == kF32 && pairs) { O2M_RES_D(kF32, true, false) }
+    else if (et == kF32) { O2M_RES_D(kF32, false, false) }
+    else if (et == kI32) O2M_RES(kI32, 1, false, false, false);
     else return hipErrorInvalidValue;
 #undef O2M_RES_D
 #undef O2M_RES

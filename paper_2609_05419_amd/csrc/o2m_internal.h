@@ -164,12 +164,6 @@ struct CsCombineArgs {
 };
 hipError_t launch_cs_combine(ElemType et, const CsCombineArgs &g, hipStream_t st);
 // K2: quantize + residues + 2M pre into operand planes.
-//   mode 0: operand rows are rows of X (A, m x k), element (r, kk) at X[r + kk*ld]
-//   mode 1: operand rows are columns of X (B, k x n), element (r, kk) at X[kk + r*ld]
-//   mode 2: SYRK, X real n x k, element (r, kk) = X[r + kk*ld] + i X[r + (kk+kh)*ld]
-//   shift: quantization shift p (value scaled by 2^(p - E_r)); E may be NULL (gauss).
-//   digits: base-2^26 digits of the quantized values, from their bound
-//   (residue_digits).
 // Plane 2l receives X+ and plane 2l+1 receives X-; the source's k-block j
 // lands in k-block j + kofs_p of the + plane and j + kofs_m of the - plane
 // (rank-2k updates concatenate two sources along k; otherwise both are 0).
@@ -182,9 +176,24 @@ struct PlaneGeom {
     size_t plane_bytes;  // rows_pad * plane_kblocks * 64
     int conj;            // 1: the operand is conj(X) (a conjugate-transposed GEMM operand)
 };
-hipError_t launch_residues(int mode, ElemType et, const void *X, int ld, const int32_t *E, int shift,
-                           int digits, int khalf, const PlaneGeom &g, const ResidueParams &rp,
-                           int8_t *planes, hipStream_t st);
+// One operand of a residue launch.
+//   mode 0: operand rows are rows of X (A, m x k), element (r, kk) at X[r + kk*ld]
+//   mode 1: operand rows are columns of X (B, k x n), element (r, kk) at X[kk + r*ld]
+//   split (SYRK; the launch's flag): X real n x k, rows, element
+//   (r, kk) = X[r + kk*ld] + i X[r + (kk+khalf)*ld]
+struct ResidueSource {
+    const void *X;
+    int ld, mode;
+    const int32_t *E;    // row exponents (gauss: unused)
+    int shift;           // quantization shift p (value scaled by 2^(p - E_r))
+    int digits;          // base-2^26 digits of the quantized values (residue_digits)
+    int khalf;
+    PlaneGeom g;
+    int8_t *planes;
+};
+// One or two sources, in one launch where their digits and load widths agree.
+hipError_t launch_residues(ElemType et, bool split, int count, const ResidueSource *src, const ResidueParams &rp,
+                           hipStream_t st);
 // Digits for quantized values below 2^bits: 1 up to 44 bits (no split), 2 up
 // to 62, 3 up to 88 (top digit < 2^36), 4 up to 108 and 5 up to 134 (top digit
 // < 2^30, int32); 0 if more are needed.

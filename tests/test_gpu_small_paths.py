@@ -1,0 +1,91 @@
+"""GPU parity of the kernels' paths for small and ragged problems with the CPU
+oracle, whole outputs bit for bit (every output is one correctly rounded
+value, so there is no tolerance)."""
+import numpy as np
+import pytest
+
+import oracle as O
+import workloads as W
+from conftest import same_bits
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def o2m():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2609_05419_amd as lib
+    return lib
+
+
+def to_dev(x):
+    return torch.from_numpy(np.ascontiguousarray(np.asarray(x).T)).to(DEV).t()
+
+
+def padded(x, pad):
+    """to_dev with a leading dimension of rows + pad."""
+    rows, cols = x.shape
+    buf = torch.full((cols, rows + pad), float("nan"), dtype=torch.from_numpy(x).dtype, device=DEV)
+    buf[:, :rows] = to_dev(x).t()
+    return buf[:, :rows].t()
+
+
+def host(t):
+    torch.cuda.synchronize()
+    return np.asfortranarray(t.cpu().numpy())
+
+
+def op_of(x, t):
+    return x if t == "N" else x.T if t == "T" else x.conj().T
+
+
+# ------------------------------------------------------------------ residues
+# Fragments are 16 rows x 64 k: sizes one below, at and one above both; one
+# fragment row with padding beside it; the moduli split in parts (fewer than
+# 2048 waves) at odd counts, with a hybrid set cut inside its 2M and 3M moduli;
+# the two operands' digit counts apart (N = 13, k = 65 and N = 26, k = 17: two
+# launches); fp32 pairs with an odd row or k at the edge, and no pairs (odd
+# leading dimension); clamped indices must not read the NaN beyond the operand.
+RESIDUES = [
+    # call, m, n, k, N, rule, transa, transb, pad
+    ("z", 15, 17, 63, 16, "max", "N", "N", 1),
+    ("z", 16, 16, 64, 16, "cs", "T", "N", 0),
+    ("z", 17, 15, 65, 7, "max", "C", "T", 3),
+    ("z", 1, 1, 1, 3, "max", "N", "N", 0),
+    ("z", 33, 1, 129, 26, "cs", "N", "T", 2),
+    ("z", 40, 50, 65, 13, "max", "N", "N", 0),
+    ("z", 40, 50, 17, 26, "max", "N", "N", 0),
+    ("z", 30, 70, 70, 31, "max", "T", "C", 0),
+    ("c", 17, 31, 65, 8, "max", "N", "N", 1),
+    ("c", 33, 15, 63, 8, "cs", "T", "T", 1),
+    ("c", 31, 47, 127, 5, "max", "N", "C", 2),
+    ("c", 16, 48, 66, 8, "max", "C", "N", 2),
+]
+
+
+@pytest.mark.parametrize("case", RESIDUES, ids=["-".join(str(v) for v in c) for c in RESIDUES])
+def test_residue_edges(o2m, case):
+    call, m, n, k, N, rule, ta, tb, pad = case
+    dt = np.complex64 if call == "c" else np.complex128
+    a = W.complex_matrix(*((m, k) if ta == "N" else (k, m)), seed=900 + m, dist="phi", phi=1.0, dtype=dt)
+    b = W.complex_matrix(*((k, n) if tb == "N" else (n, k)), seed=901 + n, dist="phi", phi=1.0, dtype=dt)
+    fn, ref = (o2m.cgemm_2m_op, O.oq_cgemm) if call == "c" else (o2m.zgemm_2m_op, O.oq_zgemm)
+    got = host(fn(padded(a, pad), padded(b, pad), ta, tb, n_moduli=N, scaling=rule))
+    assert same_bits(got, ref(op_of(a, ta), op_of(b, tb), N, scaling=rule))
+
+
+@pytest.mark.parametrize("n,k,N,rule", [(17, 64, 16, "max"), (16, 63, 11, "cs"), (31, 129, 18, "max"), (1, 1, 16, "cs")])
+def test_residue_edges_symmetric(o2m, n, k, N, rule):
+    """Rank-2k sources in one launch, and the real split with odd k (its
+    imaginary half ends one column before its k does)."""
+    a, b = (W.complex_matrix(n, k, s, dist="phi", phi=1.0) for s in (71, 72))
+    ra, rb = (W.real_matrix(n, k, s, dist="phi", phi=1.0) for s in (73, 74))
+    tri = np.tril_indices(n)
+    for got, ref in ((o2m.zher2k_2m(padded(a, 1), padded(b, 2), n_moduli=N, scaling=rule), O.oq_zher2k(a, b, N, scaling=rule)),
+                     (o2m.dsyr2k_2m(padded(ra, 1), padded(rb, 2), n_moduli=N, scaling=rule), O.oq_dsyr2k(ra, rb, N, scaling=rule)),
+                     (o2m.dsyrk_2m(padded(ra, 1), n_moduli=N, scaling=rule), O.oq_dsyrk(ra, N, scaling=rule))):
+        assert same_bits(host(got)[tri], np.asarray(ref)[tri])
