@@ -204,6 +204,14 @@ o2m_status zher2k_2m_ex(char uplo, int n, int k, const double *A, int lda, const
 o2m_status dsyr2k_2m_ex(char uplo, int n, int k, const double *A, int lda, const double *B, int ldb,
                         double *C, int ldc, int n_moduli, int scaling, void *stream);
 
+/* The symmetric calls for a fresh output: op 'h' (zherk_2m_ex), 's'
+   (dsyrk_2m_ex), 'x' (zher2k_2m_ex) or 'y' (dsyr2k_2m_ex); the other strict
+   triangle of the n x n C is set to zero by the kernel that writes the
+   computed one.  B is used by 'x' and 'y' only.  Errors as from the call that
+   op names; -1 also for an unknown op. */
+o2m_status o2m_sym_fresh(char op, char uplo, int n, int k, const double *A, int lda, const double *B, int ldb,
+                         double *C, int ldc, int n_moduli, int scaling, void *stream);
+
 /* C = op(A) op(B) (Section 3.2, Algorithm 1, on the operands op(A), op(B)),
    with op(X) = X for 'N', X^T for 'T' and X^H for 'C' (either case), BLAS
    style: op(A) is m x k, stored as A (m x k, lda >= m) for 'N' or as an

@@ -46,6 +46,7 @@ _L.zherk_2m_ex.argtypes = [_C, _I, _I, _P, _I, _P, _I, _I, _I, _P]
 _L.dsyrk_2m_ex.argtypes = [_C, _I, _I, _P, _I, _P, _I, _I, _I, _P]
 _L.zher2k_2m_ex.argtypes = [_C, _I, _I, _P, _I, _P, _I, _P, _I, _I, _I, _P]
 _L.dsyr2k_2m_ex.argtypes = [_C, _I, _I, _P, _I, _P, _I, _P, _I, _I, _I, _P]
+_L.o2m_sym_fresh.argtypes = [_C, _C, _I, _I, _P, _I, _P, _I, _P, _I, _I, _I, _P]
 _L.gauss_gemm_2m.argtypes = [_I, _I, _I, _P, _I, _P, _I, _P, _I, _I, _P]
 _L.zgemm_2m_residues.argtypes = [_I, _I, _I, _P, _I, _P, _I, _I, _P, _P, _P, _P]
 _L.zgemm_2m_residues_ex.argtypes = [_I, _I, _I, _P, _I, _P, _I, _I, _I, _P, _P, _P, _P]
@@ -62,7 +63,7 @@ _L.o2m_phase_times.argtypes = [_P, _I]
 _L.o2m_status_string.argtypes = [_I]
 _L.o2m_status_string.restype = ctypes.c_char_p
 for _f in ("zgemm_2m", "zgemm_2m_noalloc", "cgemm_2m", "zherk_2m", "dsyrk_2m", "zher2k_2m", "dsyr2k_2m", "zgemm_2m_ex",
-           "cgemm_2m_ex", "zgemm_2m_op", "cgemm_2m_op", "zherk_2m_ex", "dsyrk_2m_ex", "zher2k_2m_ex", "dsyr2k_2m_ex", "gauss_gemm_2m",
+           "cgemm_2m_ex", "zgemm_2m_op", "cgemm_2m_op", "zherk_2m_ex", "dsyrk_2m_ex", "zher2k_2m_ex", "dsyr2k_2m_ex", "o2m_sym_fresh", "gauss_gemm_2m",
            "zgemm_2m_residues", "zgemm_2m_residues_ex", "o2m_moduli", "o2m_budget", "o2m_shifts",
            "o2m_set_workspace", "o2m_release_workspace", "o2m_get_status", "o2m_phase_timing",
            "o2m_phase_times"):
@@ -203,8 +204,15 @@ def cgemm_2m_op(A: torch.Tensor, B: torch.Tensor, transa: str = "N", transb: str
                     scaling)
 
 
-def _sym_out(out, n, dtype, device):
-    return colmajor(torch.zeros((n, n), dtype=dtype, device=device)) if out is None else out
+def _sym_fresh(op: bytes, name: str, A, B, n_moduli, stream, scaling, uplo):
+    """The symmetric call ``op`` into a fresh output, whose other strict
+    triangle the library sets to zero."""
+    n, k = A.shape
+    out = _empty_colmajor(n, n, A.dtype, A.device)
+    b, ldb = (B.data_ptr(), _ld(B)) if B is not None else (None, 1)
+    _check(_L.o2m_sym_fresh(op, _uplo(uplo), n, k, A.data_ptr(), _ld(A), b, ldb, out.data_ptr(), _ld(out), n_moduli,
+                            _rule(scaling), _stream(stream)), name)
+    return out
 
 
 def _uplo(uplo: str) -> bytes:
@@ -220,8 +228,9 @@ def zherk_2m(A: torch.Tensor, n_moduli: int = 16, out: torch.Tensor | None = Non
     of ``out`` it is left alone."""
     if A.dtype != torch.complex128 or not A.is_cuda:
         raise TypeError("A must be a complex128 device tensor")
+    if out is None:
+        return _sym_fresh(b"h", "zherk_2m", A, None, n_moduli, stream, scaling, uplo)
     n, k = A.shape
-    out = _sym_out(out, n, torch.complex128, A.device)
     _check(_L.zherk_2m_ex(_uplo(uplo), n, k, A.data_ptr(), _ld(A), out.data_ptr(), _ld(out), n_moduli,
                           _rule(scaling), _stream(stream)), "zherk_2m")
     return out
@@ -233,8 +242,9 @@ def dsyrk_2m(A: torch.Tensor, n_moduli: int = 16, out: torch.Tensor | None = Non
     2M HERK."""
     if A.dtype != torch.float64 or not A.is_cuda:
         raise TypeError("A must be a float64 device tensor")
+    if out is None:
+        return _sym_fresh(b"s", "dsyrk_2m", A, None, n_moduli, stream, scaling, uplo)
     n, k = A.shape
-    out = _sym_out(out, n, torch.float64, A.device)
     _check(_L.dsyrk_2m_ex(_uplo(uplo), n, k, A.data_ptr(), _ld(A), out.data_ptr(), _ld(out), n_moduli,
                           _rule(scaling), _stream(stream)), "dsyrk_2m")
     return out
@@ -252,8 +262,9 @@ def zher2k_2m(A: torch.Tensor, B: torch.Tensor, n_moduli: int = 16, out: torch.T
               stream=None, scaling: str = "max", uplo: str = "L") -> torch.Tensor:
     """Lower or upper triangle of C = A B^H + B A^H (complex128 A, B: n x k)."""
     _check_pair(A, B, torch.complex128)
+    if out is None:
+        return _sym_fresh(b"x", "zher2k_2m", A, B, n_moduli, stream, scaling, uplo)
     n, k = A.shape
-    out = _sym_out(out, n, torch.complex128, A.device)
     _check(_L.zher2k_2m_ex(_uplo(uplo), n, k, A.data_ptr(), _ld(A), B.data_ptr(), _ld(B), out.data_ptr(), _ld(out),
                            n_moduli, _rule(scaling), _stream(stream)), "zher2k_2m")
     return out
@@ -264,8 +275,9 @@ def dsyr2k_2m(A: torch.Tensor, B: torch.Tensor, n_moduli: int = 16, out: torch.T
     """Lower or upper triangle of C = A B^T + B A^T (float64 A, B: n x k) via
     the half-k 2M HER2K."""
     _check_pair(A, B, torch.float64)
+    if out is None:
+        return _sym_fresh(b"y", "dsyr2k_2m", A, B, n_moduli, stream, scaling, uplo)
     n, k = A.shape
-    out = _sym_out(out, n, torch.float64, A.device)
     _check(_L.dsyr2k_2m_ex(_uplo(uplo), n, k, A.data_ptr(), _ld(A), B.data_ptr(), _ld(B), out.data_ptr(), _ld(out),
                            n_moduli, _rule(scaling), _stream(stream)), "dsyr2k_2m")
     return out

@@ -280,6 +280,7 @@ struct Call {
     bool noalloc = false;     // workspace = the static scratch array
     char ta = 'N', tb = 'N';  // GEMM operands: op(X) = X, X^T or X^H ('N', 'T', 'C')
     bool upper = false;       // symmetric ops: write the upper triangle
+    bool zero_other = false;  // and zeros to the other strict triangle
 };
 
 bool is_sym(Op op) { return op == kOpH || op == kOpS || op == kOpH2 || op == kOpS2; }
@@ -441,6 +442,7 @@ o2m_status run(const Call &c) {
     ca.k = c.k;
     ca.status = status;
     ca.upper = c.upper;
+    ca.zero_other = c.zero_other;
     for (int l = 0; l < c.N; ++l) {
         ca.hmod[l] = (short)t->res.mod[l];
         ca.hroot[l] = (short)t->res.root[l];
@@ -573,6 +575,19 @@ o2m_status gemm_op(Op op, char transa, char transb, int m, int n, int k, const v
     return run(c);
 }
 
+// The symmetric calls: checks, then the call (zero_other: see Call).
+o2m_status sym_call(Op op, char uplo, int n, int k, const double *A, int lda, const double *B, int ldb, double *C,
+                    int ldc, int n_moduli, int scaling, bool zero_other, void *stream) {
+    o2m_status s = is_rank2(op) ? check_sym2(uplo, n, k, A, lda, B, ldb, C, ldc, n_moduli, is_real_split(op))
+                                : check_sym(uplo, n, k, A, lda, C, ldc, n_moduli);
+    if (s == O2M_OK) s = check_scaling(scaling);
+    if (s != O2M_OK || n == 0) return s;
+    Call c{op, n, n, k, A, lda, B, ldb, C, ldc, n_moduli, scaling, (hipStream_t)stream, nullptr, nullptr, nullptr};
+    c.upper = uplo == 'U' || uplo == 'u';
+    c.zero_other = zero_other;
+    return run(c);
+}
+
 }  // namespace
 
 extern "C" {
@@ -627,13 +642,7 @@ o2m_status cgemm_2m(int m, int n, int k, const float *A, int lda, const float *B
 
 o2m_status zherk_2m_ex(char uplo, int n, int k, const double *A, int lda, double *C, int ldc, int n_moduli,
                        int scaling, void *stream) {
-    o2m_status s = check_sym(uplo, n, k, A, lda, C, ldc, n_moduli);
-    if (s == O2M_OK) s = check_scaling(scaling);
-    if (s != O2M_OK || n == 0) return s;
-    Call c{kOpH, n, n, k, A, lda, nullptr, 1, C, ldc, n_moduli, scaling, (hipStream_t)stream, nullptr,
-                    nullptr, nullptr};
-    c.upper = uplo == 'U' || uplo == 'u';
-    return run(c);
+    return sym_call(kOpH, uplo, n, k, A, lda, nullptr, 1, C, ldc, n_moduli, scaling, false, stream);
 }
 
 o2m_status zherk_2m(char uplo, int n, int k, const double *A, int lda, double *C, int ldc, int n_moduli,
@@ -643,13 +652,7 @@ o2m_status zherk_2m(char uplo, int n, int k, const double *A, int lda, double *C
 
 o2m_status dsyrk_2m_ex(char uplo, int n, int k, const double *A, int lda, double *C, int ldc, int n_moduli,
                        int scaling, void *stream) {
-    o2m_status s = check_sym(uplo, n, k, A, lda, C, ldc, n_moduli);
-    if (s == O2M_OK) s = check_scaling(scaling);
-    if (s != O2M_OK || n == 0) return s;
-    Call c{kOpS, n, n, k, A, lda, nullptr, 1, C, ldc, n_moduli, scaling, (hipStream_t)stream, nullptr,
-                    nullptr, nullptr};
-    c.upper = uplo == 'U' || uplo == 'u';
-    return run(c);
+    return sym_call(kOpS, uplo, n, k, A, lda, nullptr, 1, C, ldc, n_moduli, scaling, false, stream);
 }
 
 o2m_status dsyrk_2m(char uplo, int n, int k, const double *A, int lda, double *C, int ldc, int n_moduli,
@@ -659,13 +662,7 @@ o2m_status dsyrk_2m(char uplo, int n, int k, const double *A, int lda, double *C
 
 o2m_status zher2k_2m_ex(char uplo, int n, int k, const double *A, int lda, const double *B, int ldb, double *C,
                         int ldc, int n_moduli, int scaling, void *stream) {
-    o2m_status s = check_sym2(uplo, n, k, A, lda, B, ldb, C, ldc, n_moduli, false);
-    if (s == O2M_OK) s = check_scaling(scaling);
-    if (s != O2M_OK || n == 0) return s;
-    Call c{kOpH2, n, n, k, A, lda, B, ldb, C, ldc, n_moduli, scaling, (hipStream_t)stream, nullptr,
-                    nullptr, nullptr};
-    c.upper = uplo == 'U' || uplo == 'u';
-    return run(c);
+    return sym_call(kOpH2, uplo, n, k, A, lda, B, ldb, C, ldc, n_moduli, scaling, false, stream);
 }
 
 o2m_status zher2k_2m(char uplo, int n, int k, const double *A, int lda, const double *B, int ldb, double *C,
@@ -675,13 +672,15 @@ o2m_status zher2k_2m(char uplo, int n, int k, const double *A, int lda, const do
 
 o2m_status dsyr2k_2m_ex(char uplo, int n, int k, const double *A, int lda, const double *B, int ldb, double *C,
                         int ldc, int n_moduli, int scaling, void *stream) {
-    o2m_status s = check_sym2(uplo, n, k, A, lda, B, ldb, C, ldc, n_moduli, true);
-    if (s == O2M_OK) s = check_scaling(scaling);
-    if (s != O2M_OK || n == 0) return s;
-    Call c{kOpS2, n, n, k, A, lda, B, ldb, C, ldc, n_moduli, scaling, (hipStream_t)stream, nullptr,
-                    nullptr, nullptr};
-    c.upper = uplo == 'U' || uplo == 'u';
-    return run(c);
+    return sym_call(kOpS2, uplo, n, k, A, lda, B, ldb, C, ldc, n_moduli, scaling, false, stream);
+}
+
+o2m_status o2m_sym_fresh(char op, char uplo, int n, int k, const double *A, int lda, const double *B, int ldb,
+                         double *C, int ldc, int n_moduli, int scaling, void *stream) {
+    Op o;
+    if (!op_of(op, &o) || !is_sym(o)) return -1;
+    return sym_call(o, uplo, n, k, A, lda, is_rank2(o) ? B : nullptr, is_rank2(o) ? ldb : 1, C, ldc, n_moduli,
+                    scaling, true, stream);
 }
 
 o2m_status dsyr2k_2m(char uplo, int n, int k, const double *A, int lda, const double *B, int ldb, double *C,

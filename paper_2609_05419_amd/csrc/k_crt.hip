@@ -236,6 +236,10 @@ __global__ __launch_bounds__(256, T <= 3 ? 6 : 1) void crt_kernel(CrtArgs a, Crt
 // straight into LDS were slower for it).  The rows' exponents are fetched
 // before the limb sums; the complex form is held to 80 registers up to three
 // limbs (six waves per SIMD) and 96 with four (five).
+// A fresh output's other triangle gets its zeros here (zero_other), with the
+// mirrored tiles: n(n-1)/2 entries written once.  A fill of the whole matrix
+// and its transposition before the call took 214 us for 4096 x 4096 complex
+// and 122 us for 3001 x 3001 real.
 template <int T, bool REAL_ONLY>
 __global__ __launch_bounds__(256, REAL_ONLY ? 1 : (T <= 3 ? 6 : 5)) void crt_sym_kernel(CrtArgs a, CrtParams cp) {
     constexpr int CH = REAL_ONLY ? 8 : 4;  // planes per chunk
@@ -251,6 +255,18 @@ __global__ __launch_bounds__(256, REAL_ONLY ? 1 : (T <= 3 ? 6 : 5)) void crt_sym
     // the thread's entries: rows r0 + 8e (e = 0..3) of column jl, so that each
     // store writes whole 128-byte lines across 8 lanes
     const int jl = tid >> 3, r0 = tid & 7;
+
+    // a fresh output: zeros to the mirrored tile's strict other triangle, in
+    // the same layout, while the first copies are on their way
+    if (a.zero_other) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int i = J * 32 + r0 + 8 * e, j = I * 32 + jl;
+            if (i >= a.n || j >= a.n || (a.upper ? i <= j : i >= j)) continue;
+            if (REAL_ONLY) reinterpret_cast<double *>(a.c)[(size_t)i + (size_t)j * a.ldc] = 0.0;
+            else reinterpret_cast<double2 *>(a.c)[(size_t)i + (size_t)j * a.ldc] = make_double2(0.0, 0.0);
+        }
+    }
 
     // each thread copies 16 bytes (half a column of P or of Q) of the chunk's
     // planes of one parity: planes l0 + po, l0 + po + 2, ..

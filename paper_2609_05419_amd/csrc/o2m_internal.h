@@ -246,6 +246,7 @@ struct CrtArgs {
     int k;
     int *status;
     int upper;          // HERK/SYRK/rank-2k: write the upper triangle instead of the lower
+    int zero_other;     // and zeros to the other strict triangle
     short hmod[kMaxModuli], hroot[kMaxModuli];  // hook mode: moduli and roots
 };
 // Both go to the CRT kernels by value: stay within the kernel-argument limit.
