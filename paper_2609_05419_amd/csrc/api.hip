@@ -63,6 +63,8 @@ hipEvent_t g_events[kMaxTimedCalls][kPhaseCount + 1];
 bool g_events_made[kMaxTimedCalls];
 int g_timed_calls = 0;
 
+constexpr size_t kQueueBytes = sizeof(unsigned) * 8 * kQueueStride;
+
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct Carver {
@@ -147,7 +149,7 @@ size_t carve(const Geometry &g, int N, void *base, Buffers *b) {
     // where E begins: K1 clears them with one fill
     t.amax_a = (unsigned long long *)c.take(sizeof(unsigned long long) * g.a_pad);
     t.amax_b = g.shared_planes ? t.amax_a : (unsigned long long *)c.take(sizeof(unsigned long long) * g.b_pad);
-    t.queue = (unsigned *)c.take(sizeof(unsigned) * 8 * kQueueStride);
+    t.queue = (unsigned *)c.take(kQueueBytes);
     t.E = (int32_t *)c.take(sizeof(int32_t) * g.a_pad);
     t.F = g.shared_planes ? t.E : (int32_t *)c.take(sizeof(int32_t) * g.b_pad);
     // every record the combine step reads is written by the scan: no fill
@@ -332,20 +334,60 @@ o2m_status run(const Call &c) {
 
     const ElemType et = c.op == kOpC ? kF32 : c.op == kOpG ? kI32 : is_real_split(c.op) ? kR64 : kF64;
 
+    // the int8 GEMM's launch (K3)
+    GemmArgs gm;
+    memset(&gm, 0, sizeof gm);
+    gm.a = b.planes_a;
+    gm.b = sym ? b.planes_a + g.plane_a : b.planes_b;
+    gm.c = b.res;
+    gm.queue = b.queue;
+    gm.a_pstride = sym ? 2 * g.plane_a : g.plane_a;
+    gm.b_pstride = sym ? 2 * g.plane_a : g.plane_b;
+    gm.c_pstride = g.plane_c;
+    gm.mt = g.a_pad / kRowBlock;
+    gm.nt = g.b_pad / kRowBlock;
+    gm.kblocks = g.halves * g.kblocks;
+    gm.batch = g.products;
+    gm.ldc = g.a_pad;
+    for (int p = 0; p < g.products; ++p) {   // product -> modulus
+        const int n2 = t->res.n2;
+        const int l = sym ? p : p < 2 * n2 ? p >> 1 : n2 + (p - 2 * n2) / 3;
+        gm.mod[p] = t->res.mod[l];
+        gm.inv[p] = t->res.inv[l];
+    }
+
     const int slot = phase_begin();
     phase_mark(slot, 0, c.st);
     // ---- K1: maxima and exponents (rank-2k: row i of A and of B share one) --
-    // the maxima (max rule) and the GEMM's slot counters start at zero: one
-    // fill over the contiguous amax_a .. queue region of the workspace (carve
-    // order)
-    O2M_TRY(launch_zero(b.amax_a, (size_t)((char *)b.E - (char *)b.amax_a), c.st));
     // where the operand rows sit: A's rows are rows of the stored A (mode 0)
     // or, transposed, its columns (mode 1); B's operand rows (the columns of
     // op(B)) are columns of the stored B (mode 1) or, transposed, its rows
     const int amode = c.ta == 'N' ? 0 : 1, bmode = c.tb == 'N' ? 1 : 0;
     const int a_rows = amode == 0 ? c.m : c.k, a_cols = amode == 0 ? c.k : c.m;  // stored A
     const int b_rows = bmode == 1 ? c.k : c.n, b_cols = bmode == 1 ? c.n : c.k;  // stored B
-    if (cs && c.op != kOpG) {
+    CsCombineArgs cg;
+    memset(&cg, 0, sizeof cg);
+    cg.ca = c.m;
+    cg.cb = sym ? 0 : c.n;
+    cg.Ea = b.E;
+    cg.Eb = b.F;
+    cg.status = status;
+    cg.A = c.A;
+    cg.lda = c.lda;
+    cg.B2 = two ? c.B : nullptr;
+    cg.ldb2 = c.ldb;
+    cg.B = sym ? nullptr : c.B;
+    cg.ldb = c.ldb;
+    cg.k = c.k;
+    cg.amode = amode;
+    cg.bmode = bmode;
+    const bool gauss = c.op == kOpG;
+    if (direct_applies(et, cg)) {
+        if (gemm_uses_queue(gm)) O2M_TRY(launch_zero(b.queue, kQueueBytes, c.st));
+        O2M_TRY(launch_exponents_direct(et, cs && !gauss, cg, gauss ? b.amax_a : nullptr, gauss ? b.amax_b : nullptr,
+                                        c.st));
+    } else if (cs && !gauss) {
+        if (gemm_uses_queue(gm)) O2M_TRY(launch_zero(b.queue, kQueueBytes, c.st));
         // one pass over each operand: chunk records, then the exponents they
         // settle (the few entries they leave open are summed from the data)
         b.csa.chunks = cs_chunks(amode, a_rows, a_cols) * g.halves;
@@ -353,30 +395,17 @@ o2m_status run(const Call &c) {
         O2M_TRY(launch_cs_scan(amode, et, a_rows, a_cols, c.A, c.lda, b.csa, 0, c.st));
         if (two) O2M_TRY(launch_cs_scan(0, et, c.m, c.k, c.B, c.ldb, b.csa, b.csa.chunks / 2, c.st));
         if (!sym) O2M_TRY(launch_cs_scan(bmode, et, b_rows, b_cols, c.B, c.ldb, b.csb, 0, c.st));
-        CsCombineArgs cg;
-        memset(&cg, 0, sizeof cg);
-        cg.ca = c.m;
-        cg.cb = sym ? 0 : c.n;
         cg.pa = b.csa;
         cg.pb = b.csb;
-        cg.Ea = b.E;
-        cg.Eb = b.F;
-        cg.status = status;
-        cg.A = c.A;
-        cg.lda = c.lda;
-        cg.B2 = two ? c.B : nullptr;
-        cg.ldb2 = c.ldb;
-        cg.B = sym ? nullptr : c.B;
-        cg.ldb = c.ldb;
-        cg.k = c.k;
-        cg.amode = amode;
-        cg.bmode = bmode;
         O2M_TRY(launch_cs_combine(et, cg, c.st));
     } else {
+        // the maxima and the GEMM's slot counters start at zero: one fill over
+        // the contiguous amax_a .. queue region of the workspace (carve order)
+        O2M_TRY(launch_zero(b.amax_a, (size_t)((char *)b.E - (char *)b.amax_a), c.st));
         O2M_TRY(launch_amax(amode, et, a_rows, a_cols, c.A, c.lda, b.amax_a, c.st));
         if (two) O2M_TRY(launch_amax(0, et, c.m, c.k, c.B, c.ldb, b.amax_a, c.st));
         if (!sym) O2M_TRY(launch_amax(bmode, et, b_rows, b_cols, c.B, c.ldb, b.amax_b, c.st));
-        if (c.op != kOpG)
+        if (!gauss)
             O2M_TRY(launch_exponents(c.m, b.amax_a, b.E, sym ? 0 : c.n, b.amax_b, b.F, status, c.st));
     }
     phase_mark(slot, 1, c.st);
@@ -401,26 +430,6 @@ o2m_status run(const Call &c) {
     phase_mark(slot, 2, c.st);
 
     // ---- K3: int8 GEMMs ----------------------------------------------------
-    GemmArgs gm;
-    memset(&gm, 0, sizeof gm);
-    gm.a = b.planes_a;
-    gm.b = sym ? b.planes_a + g.plane_a : b.planes_b;
-    gm.c = b.res;
-    gm.queue = b.queue;
-    gm.a_pstride = sym ? 2 * g.plane_a : g.plane_a;
-    gm.b_pstride = sym ? 2 * g.plane_a : g.plane_b;
-    gm.c_pstride = g.plane_c;
-    gm.mt = g.a_pad / kRowBlock;
-    gm.nt = g.b_pad / kRowBlock;
-    gm.kblocks = pkb;
-    gm.batch = g.products;
-    gm.ldc = g.a_pad;
-    for (int p = 0; p < g.products; ++p) {   // product -> modulus
-        const int n2 = t->res.n2;
-        const int l = sym ? p : p < 2 * n2 ? p >> 1 : n2 + (p - 2 * n2) / 3;
-        gm.mod[p] = t->res.mod[l];
-        gm.inv[p] = t->res.inv[l];
-    }
     O2M_TRY(launch_gemm(gm, c.st));
     phase_mark(slot, 3, c.st);
 

@@ -432,6 +432,11 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_i8_kernel(GemmArgs g) {
 
 }  // namespace
 
+bool gemm_uses_queue(const GemmArgs &ga) {
+    const GemmSchedule sc = gemm_plan(ga.mt, ga.nt, ga.kblocks, ga.batch, kStageBytes);
+    return sc.fixed < sc.slots;
+}
+
 hipError_t launch_gemm(const GemmArgs &ga_in, hipStream_t st) {
     static_assert(kThreads * 16 * kLoadsPerStage == 2 * kStageBytes, "stage copy covers A and B");
     GemmArgs ga = ga_in;

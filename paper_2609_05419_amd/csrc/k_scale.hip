@@ -24,6 +24,8 @@
 #include "o2m_internal.h"
 #include "cs_bounds.h"
 
+#include <string.h>
+
 namespace o2m {
 namespace {
 
@@ -413,6 +415,131 @@ __global__ __launch_bounds__(64 * kCombineWaves) void cs_combine_kernel(CsCombin
     }
 }
 
+// ---- exponents straight from the operands --------------------------------
+// One launch finds the exponents of both sides: a workgroup of 16 waves takes
+// RB operand rows with all their entries, so that nothing has to be combined
+// across workgroups and no buffer has to be cleared first.  Rows of a
+// column-major X: a workgroup takes 16 rows (64 measured 1.4-2x slower below
+// 2048 rows: too few workgroups), thread t row t % 16 of every 64th column;
+// columns of X: a wave per column.  Both rules: the maximum first, then
+// (Cauchy-Schwarz) the rule's sum against it, over the entries held in
+// registers (HOLD, up to kHold per thread) or read again.
+// Bound at these sizes: launches and load latency.  Scale phase against the
+// chunked scans (3-4 launches): 96 x 80 x 200 14.4 -> 8.8 us, 500 x 333 x 777
+// 18.8 -> 11.6, 1024^3 18.1 -> 11.5 (max rule) and 22.5 -> 13.3, CGEMM
+// 1537 x 1283 x 2051 30.4 -> 18.9.
+struct DirectSide {
+    const void *X, *X2;          // X2: the second source of a rank-2k update, or null
+    int ld, ld2, mode, count, k;
+    int32_t *E;
+    unsigned long long *amax;    // gauss: the maxima themselves, instead of E
+};
+struct DirectArgs {
+    DirectSide s[2];
+    unsigned blocks0;            // workgroups of s[0]
+    int *status;
+};
+constexpr int kHold = 16;
+constexpr int kDirectK = 2560;                           // entries per operand row (direct_applies)
+constexpr size_t kDirectBytes = size_t(96) << 20;
+
+constexpr int kDirectRows = 16;   // operand rows per workgroup, either mode
+
+template <ElemType ET, bool CS, bool HOLD>
+__global__ __launch_bounds__(1024) void exponents_direct(DirectArgs a) {
+    const bool second = blockIdx.x >= a.blocks0;
+    const DirectSide &o = a.s[second ? 1 : 0];
+    const int block = (int)(blockIdx.x - (second ? a.blocks0 : 0u));
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const bool cols = o.mode == 1;
+    constexpr int RB = kDirectRows;
+    const int i = block * RB + (cols ? w : t % RB);
+    const int ic = min(i, o.count - 1), k = o.k;
+    const int c0 = cols ? lane : t / RB, step = cols ? 64 : 1024 / RB;
+    typedef typename Raw<ET>::T T;
+    // entry c of the row (clamped; zero beyond k)
+    auto entry = [&](const void *X, int ld, int c) {
+        const size_t cc = min(c, k - 1);
+        return Raw<ET>::load(X, cols ? cc + (size_t)ic * ld : (size_t)ic + cc * ld);
+    };
+    auto batch = [&](const void *X, int ld, int c, T *v, int n) {
+#pragma unroll
+        for (int u = 0; u < n; ++u) v[u] = entry(X, ld, c + u * step);
+#pragma unroll
+        for (int u = 0; u < n; ++u)
+            if (c + u * step >= k) v[u] = Raw<ET>::zero();
+    };
+    // f over all entries of this thread
+    T held[HOLD ? kHold : 1];
+    auto each = [&](auto f) {
+        if constexpr (HOLD) {
+#pragma unroll
+            for (int u = 0; u < kHold; ++u) f(held[u]);
+        } else {
+            for (int src = 0; src < 2; ++src) {
+                const void *X = src ? o.X2 : o.X;
+                if (!X) continue;
+                for (int c = c0; c < k; c += kBatch * step) {
+                    T v[kBatch];
+                    batch(X, src ? o.ld2 : o.ld, c, v, kBatch);
+#pragma unroll
+                    for (int u = 0; u < kBatch; ++u) f(v[u]);
+                }
+            }
+        }
+    };
+    __shared__ unsigned long long sm[2][16][RB];
+    // op over the row's threads (both reductions use it, each its own sm)
+    auto reduce = [&](unsigned long long v, int use, auto op) {
+        if (cols) {
+            for (int off = 32; off > 0; off >>= 1) v = op(v, __shfl_xor(v, off, 64));
+            return v;
+        }
+#pragma unroll
+        for (int off = RB; off < 64; off <<= 1) v = op(v, __shfl_xor(v, off, 64));
+        if (lane < RB) sm[use][w][lane] = v;
+        __syncthreads();
+        v = sm[use][0][t % RB];
+#pragma unroll
+        for (int q = 1; q < 16; ++q) v = op(v, sm[use][q][t % RB]);
+        return v;
+    };
+
+    unsigned long long best = 0;
+    if (k > 0) {
+        if constexpr (HOLD) batch(o.X, o.ld, c0, held, kHold);
+        each([&](T v) { best = umax(best, Raw<ET>::bits(v)); });
+    }
+    best = reduce(best, 0, [](unsigned long long x, unsigned long long y) { return umax(x, y); });
+    const bool bad = best >= 0x7FF0000000000000ull;
+    int e = bad || best == 0 ? 0 : exponent_of(best);
+    if constexpr (CS) {
+        // ceil(|v| 2^(20 - e))^2 as in ssq_term; a thread's terms, at most
+        // 2^40 each and fewer than 2^13 (kDirectK), add exactly in fp64
+        double sum = 0.0;
+        if (!bad && best != 0)
+            each([&](T x) {
+                double p[2];
+                Raw<ET>::parts(x, p);
+#pragma unroll
+                for (int q = 0; q < Raw<ET>::n; ++q) {
+                    const double u = ceil(ldexp(fabs(p[q]), 20 - e));
+                    const double y = p[q] != 0.0 ? fmax(u, 1.0) : 0.0;
+                    sum = fma(y, y, sum);
+                }
+            });
+        unsigned long long U = (unsigned long long)sum;
+        U = reduce(U, 1, [](unsigned long long x, unsigned long long y) { return x + y; });
+        if (!bad && best != 0) e += cs_d_of(U) - 20;
+    }
+    const bool writer = (cols ? lane == 0 : t < RB) && i < o.count;
+    if (writer) {
+        if (o.amax) o.amax[i] = best;
+        else o.E[i] = bad ? INT32_MIN : e;
+        if (bad) atomicOr(a.status, kStatusNonfinite);
+    }
+}
+
 // Entries [0, ca) of (amax_a, Ea), then [0, cb) of (amax_b, Eb), in one launch.
 // A row or column holding Inf or NaN gets E = INT32_MIN and sets the device
 // status bit kStatusNonfinite (one atomic per wave that saw one).
@@ -584,6 +711,48 @@ hipError_t launch_cs_combine(ElemType et, const CsCombineArgs &g, hipStream_t st
     case kF32: cs_combine_kernel<kF32><<<blocks, 64 * kCombineWaves, 0, st>>>(g); break;
     case kR64: cs_combine_kernel<kR64><<<blocks, 64 * kCombineWaves, 0, st>>>(g); break;
     default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+// The direct kernel takes calls whose rows a workgroup reads in a few rounds
+// of loads (it walks a row alone: 300 x 300 x 4096 took 35.6 us against the
+// chunked scans' 34.1, 40 x 40 x 3000 was level, 1500 x 1500 x 2000 36.9
+// against 39.5) and whose operands the caches can hold for its second reading
+// (2048^3, 128 MiB: 52.7 against 45.7 us; 2048 x 2048 x 1024, 64 MiB: 22.9
+// against 31.2).
+bool direct_applies(ElemType et, const CsCombineArgs &g) {
+    const size_t per_row = (size_t)g.k * (g.B2 ? 2 : 1);
+    const size_t bytes = entry_bytes(et) * (per_row * (size_t)g.ca + (size_t)g.k * (size_t)g.cb);
+    return per_row <= kDirectK && bytes <= kDirectBytes;
+}
+
+template <ElemType ET, bool CS>
+static void launch_direct_t(const DirectArgs &a, bool hold, unsigned blocks, hipStream_t st) {
+    if (hold) exponents_direct<ET, CS, true><<<blocks, 1024, 0, st>>>(a);
+    else exponents_direct<ET, CS, false><<<blocks, 1024, 0, st>>>(a);
+}
+
+hipError_t launch_exponents_direct(ElemType et, bool cs, const CsCombineArgs &g, unsigned long long *amax_a,
+                                   unsigned long long *amax_b, hipStream_t st) {
+    DirectArgs a;
+    memset(&a, 0, sizeof a);
+    a.s[0] = {g.A, g.B2, g.lda, g.ldb2, g.amode, g.ca, g.k, g.Ea, amax_a};
+    a.s[1] = {g.B, nullptr, g.ldb, 0, g.bmode, g.cb, g.k, g.Eb, amax_b};
+    a.status = g.status;
+    const bool hold = !g.B2 && g.k <= 64 * kHold;
+    a.blocks0 = (unsigned)(((long)g.ca + kDirectRows - 1) / kDirectRows);
+    const unsigned n = a.blocks0 + (unsigned)(((long)g.cb + kDirectRows - 1) / kDirectRows);
+    if (n == 0) return hipSuccess;
+    if (et == kI32) launch_direct_t<kI32, false>(a, hold, n, st);
+    else if (cs) {
+        if (et == kF64) launch_direct_t<kF64, true>(a, hold, n, st);
+        else if (et == kF32) launch_direct_t<kF32, true>(a, hold, n, st);
+        else launch_direct_t<kR64, true>(a, hold, n, st);
+    } else {
+        if (et == kF64) launch_direct_t<kF64, false>(a, hold, n, st);
+        else if (et == kF32) launch_direct_t<kF32, false>(a, hold, n, st);
+        else launch_direct_t<kR64, false>(a, hold, n, st);
     }
     return hipGetLastError();
 }

@@ -163,6 +163,12 @@ struct CsCombineArgs {
                             // (B's default); B2 (rank-2k) is read as rows
 };
 hipError_t launch_cs_combine(ElemType et, const CsCombineArgs &g, hipStream_t st);
+// Either rule's exponents of both sides in one launch, straight from the
+// operands (of g: all but the chunk records); gauss: the maxima into amax_a,
+// amax_b instead.  For the calls that direct_applies to.
+bool direct_applies(ElemType et, const CsCombineArgs &g);
+hipError_t launch_exponents_direct(ElemType et, bool cs, const CsCombineArgs &g, unsigned long long *amax_a,
+                                   unsigned long long *amax_b, hipStream_t st);
 // K2: quantize + residues + 2M pre into operand planes.
 // Plane 2l receives X+ and plane 2l+1 receives X-; the source's k-block j
 // lands in k-block j + kofs_p of the + plane and j + kofs_m of the - plane
@@ -226,6 +232,8 @@ struct GemmArgs {
     double inv[kMaxProducts];
 };
 hipError_t launch_gemm(const GemmArgs &ga, hipStream_t st);
+// Whether that launch claims slots at run time: then its queue must be zero.
+bool gemm_uses_queue(const GemmArgs &ga);
 
 // K4: CRT + lift + descale.
 //   mode 0 ZGEMM  (planes 2l = C+, 2l+1 = C-), output complex

@@ -112,3 +112,94 @@ def test_fresh_symmetric_output_is_zero_elsewhere(o2m, n, k, uplo):
         keep = np.tril(np.ones((n, n), bool)) if uplo == "L" else np.triu(np.ones((n, n), bool))
         assert np.array_equal(got[keep], want[keep])
         assert same_bits(got[~keep], np.zeros(int((~keep).sum()), dt))
+
+
+# ------------------------------------------------------------------ exponents
+def _special(x, rule):
+    """Rows that decide an exponent: zero, one subnormal, one huge beside one
+    tiny, and (Cauchy-Schwarz) a sum of squares at a power of 4."""
+    from cs_inputs import straddle_vector
+    m, k = x.shape
+    x[0, :] = 0
+    if m > 3:
+        x[1, :] = 0
+        x[1, k // 2] = 5e-310j if x.dtype == np.complex128 else 1e-42j
+        x[2, 0] = 1e30
+        x[2, k - 1] = 1e-30
+    if rule == "cs" and m > 5 and k >= 192:
+        x[4, :] = straddle_vector(k, "low", dtype=x.dtype)
+        x[5, :] = straddle_vector(k, "high", dtype=x.dtype)
+    return x
+
+
+# The direct kernel takes 16 rows per workgroup, 64 entries of a row per round,
+# 16 rounds held in registers (k <= 1024), and calls up to 2560 entries per
+# row; past that the chunked scans run.
+@pytest.mark.parametrize("rule", ["max", "cs"])
+@pytest.mark.parametrize("m,n,k", [(1, 1, 1), (15, 17, 63), (16, 16, 64), (17, 15, 65), (33, 31, 1024), (18, 20, 1025),
+                                   (6, 7, 2560), (7, 6, 2561), (2, 2, 0)])
+def test_exponents(o2m, m, n, k, rule):
+    a = _special(W.complex_matrix(m, k, 41, dist="phi", phi=2.0), rule) if k else np.zeros((m, 0), np.complex128)
+    b = _special(W.complex_matrix(n, k, 42, dist="phi", phi=2.0), rule).T if k else np.zeros((0, n), np.complex128)
+    b = np.asfortranarray(b)
+    _, E, F = o2m.zgemm_2m_residues(to_dev(a), to_dev(b), n_moduli=16, scaling=rule)
+    if k:
+        E0, _, F0, _ = O.exponents(a, b, rule)
+        assert np.array_equal(E.cpu().numpy(), E0) and np.array_equal(F.cpu().numpy(), F0)
+    else:
+        assert not E.any() and not F.any()
+        return
+    for ta, tb in (("N", "N"), ("T", "T")):
+        A, B = a if ta == "N" else np.asfortranarray(a.T), b if tb == "N" else np.asfortranarray(b.T)
+        got = host(o2m.zgemm_2m_op(padded(A, 1), padded(B, 1), ta, tb, n_moduli=16, scaling=rule))
+        assert same_bits(got, O.oq_zgemm(a, b, 16, scaling=rule))
+    af, bf = (_special(W.complex_matrix(r, k, 43, dist="phi", phi=1.0).astype(np.complex64), rule) for r in (m, n))
+    bf = np.asfortranarray(bf.T)
+    assert same_bits(host(o2m.cgemm_2m(to_dev(af), to_dev(bf), n_moduli=8, scaling=rule)), O.oq_cgemm(af, bf, 8, scaling=rule))
+
+
+@pytest.mark.parametrize("rule", ["max", "cs"])
+@pytest.mark.parametrize("n,k", [(17, 65), (33, 1280), (18, 1281), (20, 2561)])
+def test_exponents_symmetric(o2m, n, k, rule):
+    """Both sources of a rank-2k update count towards the limit (1280 each)."""
+    a, b = (_special(W.complex_matrix(n, k, s, dist="phi", phi=1.0), rule) for s in (51, 52))
+    b[4:6, :] = 0                                        # the straddling rows of [A | B] are A's
+    ra, rb = a.real.copy(order="F"), b.real.copy(order="F")
+    tri = np.tril_indices(n)
+    for got, ref in ((o2m.zherk_2m(to_dev(a), scaling=rule), O.oq_zherk(a, 16, scaling=rule)),
+                     (o2m.zher2k_2m(to_dev(a), to_dev(b), scaling=rule), O.oq_zher2k(a, b, 16, scaling=rule)),
+                     (o2m.dsyrk_2m(to_dev(ra), scaling=rule), O.oq_dsyrk(ra, 16, scaling=rule)),
+                     (o2m.dsyr2k_2m(to_dev(ra), to_dev(rb), scaling=rule), O.oq_dsyr2k(ra, rb, 16, scaling=rule))):
+        assert same_bits(host(got)[tri], np.asarray(ref)[tri])
+
+
+@pytest.mark.parametrize("k", [40, 1030, 2570])
+@pytest.mark.parametrize("rule", ["max", "cs"])
+def test_exponents_nonfinite(o2m, k, rule):
+    """Inf or NaN in a row or column: NaN there, the status bit, the rest exact."""
+    m, n = 19, 21
+    a, b = W.complex_matrix(m, k, 61), W.complex_matrix(k, n, 62)
+    clean = O.oq_zgemm(a, b, 16, scaling=rule)
+    a[3, k - 1] = complex(np.nan, 1.0)
+    a[17, 0] = complex(0.0, -np.inf)
+    b[k // 2, 20] = complex(np.inf, 0.0)
+    o2m.get_status()
+    got = host(o2m.zgemm_2m(to_dev(a), to_dev(b), n_moduli=16, scaling=rule))
+    assert o2m.get_status() == o2m.STATUS_NONFINITE
+    bad = np.zeros((m, n), bool)
+    bad[[3, 17], :] = True
+    bad[:, 20] = True
+    assert np.isnan(got[bad].real).all() and np.isnan(got[bad].imag).all()
+    assert same_bits(got[~bad], clean[~bad])
+
+
+@pytest.mark.parametrize("m,n,k", [(17, 15, 65), (3, 5, 2560), (5, 3, 2561)])
+def test_gauss_maxima(o2m, m, n, k):
+    """The bound check reads the maxima of whichever kernel found them."""
+    A, B = W.gauss_matrix(m, k, 7, lo=-50, hi=50), W.gauss_matrix(k, n, 8, lo=-50, hi=50)
+    dA, dB = (torch.from_numpy(x).to(DEV).transpose(0, 1) for x in (A, B))
+    o2m.get_status()
+    got = o2m.gauss_gemm_2m(dA, dB, n_moduli=4).transpose(0, 1).cpu().numpy()
+    assert o2m.get_status() == 0 and np.array_equal(got, O.gauss_4m(A, B))
+    o2m.gauss_gemm_2m(dA, dB, n_moduli=2)                # M = 56153: the bound is far exceeded
+    assert o2m.get_status() == o2m.STATUS_OVERFLOW
