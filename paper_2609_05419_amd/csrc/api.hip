@@ -344,8 +344,6 @@ o2m_status run(const Call &c) {
     gm.a_pstride = sym ? 2 * g.plane_a : g.plane_a;
     gm.b_pstride = sym ? 2 * g.plane_a : g.plane_b;
     gm.c_pstride = g.plane_c;
-    gm.mt = g.a_pad / kRowBlock;
-    gm.nt = g.b_pad / kRowBlock;
     gm.kblocks = g.halves * g.kblocks;
     gm.batch = g.products;
     gm.ldc = g.a_pad;
@@ -355,6 +353,8 @@ o2m_status run(const Call &c) {
         gm.mod[p] = t->res.mod[l];
         gm.inv[p] = t->res.inv[l];
     }
+
+    O2M_TRY(plan_gemm(gm, g.rows_a, g.rows_b));
 
     const int slot = phase_begin();
     phase_mark(slot, 0, c.st);
@@ -383,11 +383,11 @@ o2m_status run(const Call &c) {
     cg.bmode = bmode;
     const bool gauss = c.op == kOpG;
     if (direct_applies(et, cg)) {
-        if (gemm_uses_queue(gm)) O2M_TRY(launch_zero(b.queue, kQueueBytes, c.st));
+        if (gm.fixed < gm.slots) O2M_TRY(launch_zero(b.queue, kQueueBytes, c.st));
         O2M_TRY(launch_exponents_direct(et, cs && !gauss, cg, gauss ? b.amax_a : nullptr, gauss ? b.amax_b : nullptr,
                                         c.st));
     } else if (cs && !gauss) {
-        if (gemm_uses_queue(gm)) O2M_TRY(launch_zero(b.queue, kQueueBytes, c.st));
+        if (gm.fixed < gm.slots) O2M_TRY(launch_zero(b.queue, kQueueBytes, c.st));
         // one pass over each operand: chunk records, then the exponents they
         // settle (the few entries they leave open are summed from the data)
         b.csa.chunks = cs_chunks(amode, a_rows, a_cols) * g.halves;
@@ -416,16 +416,18 @@ o2m_status run(const Call &c) {
     const int kb = g.kblocks;
     const int pkb = g.halves * kb;
     const bool split = is_real_split(c.op);
+    // operand rows up to whole tiles of the GEMM (symmetric: of either side)
+    const int wa = round_up(g.rows_a, sym ? std::max(gm.tm, gm.tn) : gm.tm), wb = round_up(g.rows_b, gm.tn);
     ResidueSource src[2];
     memset(src, 0, sizeof src);
     src[0] = {c.A, c.lda, amode, b.E, pA, digits(c.scaling, pA), split ? kc : 0,
-              {c.m, kc, c.k, g.a_pad, kb, pkb, 0, two ? kb : 0, g.plane_a, c.ta == 'C'}, b.planes_a};
+              {c.m, kc, c.k, wa, kb, pkb, 0, two ? kb : 0, g.plane_a, c.ta == 'C'}, b.planes_a};
     if (two)
         src[1] = {c.B, c.ldb, amode, b.E, pA, digits(c.scaling, pA), split ? kc : 0,
-                  {c.m, kc, c.k, g.a_pad, kb, pkb, kb, 0, g.plane_a, 0}, b.planes_a};
+                  {c.m, kc, c.k, wa, kb, pkb, kb, 0, g.plane_a, 0}, b.planes_a};
     else if (!sym)
         src[1] = {c.B, c.ldb, bmode, b.F, pB, digits(c.scaling, pB), 0,
-                  {c.n, c.k, c.k, g.b_pad, kb, kb, 0, 0, g.plane_b, c.tb == 'C'}, b.planes_b};
+                  {c.n, c.k, c.k, wb, kb, kb, 0, 0, g.plane_b, c.tb == 'C'}, b.planes_b};
     O2M_TRY(launch_residues(et, split, two || !sym ? 2 : 1, src, t->res, c.st));
     phase_mark(slot, 2, c.st);
 

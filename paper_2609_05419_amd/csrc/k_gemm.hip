@@ -37,6 +37,8 @@
 #include "o2m_internal.h"
 #include "tile_schedule.h"
 
+#include <type_traits>
+
 namespace o2m {
 namespace {
 
@@ -209,12 +211,13 @@ __device__ inline void transpose_rows(uint32_t (&d)[4]) {
 // gives each lane 16 consecutive rows of one block, so one 16-byte store per
 // lane writes 64 contiguous bytes of each of 16 columns, and the two halves of
 // the wave tile fill whole 128-byte column segments.
-__device__ inline void store_tile(const v4i (&acc)[8][8], int8_t *C, int ldc, int m, double inv) {
+template <int M, int N>
+__device__ inline void store_blocks(const v4i (&acc)[M][N], int8_t *C, int ldc, int m, double inv) {
     const uint32_t negm = (uint32_t)(-m) & 0xFFFFFFu;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
+    for (int j = 0; j < N; ++j) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
+        for (int h = 0; h < M / 4; ++h) {
             uint32_t d[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
@@ -352,7 +355,7 @@ __device__ inline void epilogue(v4i (&acc)[8][8], const Wave &w, const GemmArgs 
     const int wr = w.wave >> 1, wc = w.wave & 1;
     int8_t *C = g.c + (size_t)tc.p * g.c_pstride + (size_t)(tc.tj * 256 + wc * 128 + (w.lane & 15)) * g.ldc +
                 tc.ti * 256 + wr * 128 + 16 * (w.lane >> 4);
-    store_tile(acc, C, g.ldc, g.mod[tc.p], g.inv[tc.p]);
+    store_blocks<8, 8>(acc, C, g.ldc, g.mod[tc.p], g.inv[tc.p]);
 }
 
 __device__ inline __amdgpu_buffer_rsrc_t rsrc_a(const GemmArgs &g, const TileCoord &tc) {
@@ -430,25 +433,182 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_i8_kernel(GemmArgs g) {
     epilogue(acc, w, g, tc);
 }
 
-}  // namespace
+// ---- smaller tiles, several workgroups per CU ------------------------------
+// The same pipeline with WR x WC waves of WM x WN blocks and a ring of S
+// stages, small enough for two, three or four workgroups per CU.  A 256 x 256
+// tile spends 15k cycles in prologue and epilogue, alone on its CU, and a
+// small product has fewer of them than the part has CUs: here one workgroup's
+// prologue and epilogue run beside another's MFMAs, there are 2 to 16 times as
+// many workgroups, and ragged sizes pad to 64 or 128.  The cost is data moved
+// per MFMA (operand bytes per tile, LDS reads per MFMA), which is why large
+// products keep the large tile (gemm_plan in tile_schedule.h, with both sides
+// measured).  The copy for stage kb + S goes into the buffer that stage kb has
+// left; MFMAs, fragment reads and copies interleave as above, evenly spaced.
+template <int WR, int WC, int WM, int WN, int S> struct TileShape {
+    static constexpr int kWaveRows = WR, kWaveCols = WC;      // waves of the workgroup
+    static constexpr int kFragM = WM, kFragN = WN;            // 16 x 16 blocks of a wave
+    static constexpr int kTm = WR * WM * 16, kTn = WC * WN * 16;
+    static constexpr int kRing = S;
+    static constexpr int kABytes = kTm * kStageK, kBBytes = kTn * kStageK;
+    static constexpr int kBuf = kABytes + kBBytes;            // one stage
+    static constexpr int kLoads = kBuf / 4096;                // 4 KB per copy of the workgroup
+    static_assert(WR * WC == 4 && WM % 4 == 0 && kABytes % 4096 == 0 && kBBytes % 4096 == 0, "tile shape");
+};
 
-bool gemm_uses_queue(const GemmArgs &ga) {
-    const GemmSchedule sc = gemm_plan(ga.mt, ga.nt, ga.kblocks, ga.batch, kStageBytes);
-    return sc.fixed < sc.slots;
+// Operand rows [row0, row0 + kT) of a plane: per k-stage one contiguous piece
+// of the 16 KB block they lie in.
+__device__ inline __amdgpu_buffer_rsrc_t rows_rsrc(const int8_t *plane, int row0, int bytes, int kblocks) {
+    const int8_t *base = plane + (size_t)(row0 >> 8) * kblocks * kStageBytes + ((row0 & 255) >> 4) * kFragBytes;
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t *>(base), (short)0,
+                                             (kblocks - 1) * kStageBytes + bytes, kBufferWord3);
 }
 
-hipError_t launch_gemm(const GemmArgs &ga_in, hipStream_t st) {
+template <class T>
+__device__ inline void copy_part(__amdgpu_buffer_rsrc_t rA, __amdgpu_buffer_rsrc_t rB, int stage, int8_t *buf, int tid,
+                                 int wave, int q) {
+    constexpr int na = T::kABytes / 4096;
+    const bool isa = q < na;
+    const int off = (isa ? q : q - na) * 4096;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(isa ? rA : rB,
+                                             (lds_void *)(buf + (isa ? 0 : T::kABytes) + off + wave * 1024), 16,
+                                             tid * 16, stage * kStageBytes + off, 0, 0);
+}
+
+template <class T>
+__device__ inline v4i frag_of(const int8_t *buf, int aoff, int boff, int lane, int f) {
+    const int off = f < T::kFragM ? aoff + f * kFragBytes : boff + (f - T::kFragM) * kFragBytes;
+    return *reinterpret_cast<const v4i *>(buf + off + lane * 16);
+}
+
+template <int N>
+__device__ inline void wait_stages(int n) {   // at most n stages of N copies stay in flight
+    switch (n) {
+    case 0: wait_vm<0>(); break;
+    case 1: wait_vm<N>(); break;
+    case 2: wait_vm<2 * N>(); break;
+    case 3: wait_vm<3 * N>(); break;
+    default: wait_vm<4 * N>(); break;
+    }
+}
+
+template <class T>
+__global__ __launch_bounds__(kThreads, T::kFragM * T::kFragN > 16 ? 2 : 3) void gemm_i8_multi(GemmArgs g) {
+    constexpr int M = T::kFragM, N = T::kFragN, S = T::kRing, L = T::kLoads;
+    __shared__ __attribute__((aligned(1024))) int8_t lds[S * T::kBuf];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wr = wave / T::kWaveCols, wc = wave % T::kWaveCols;
+    const int aoff = wr * M * kFragBytes, boff = T::kABytes + wc * N * kFragBytes;
+    asm volatile("" ::"s"(g.a), "s"(g.b), "s"(g.a_pstride), "s"(g.b_pstride), "s"(g.kblocks), "s"(g.mt),
+                 "s"(g.nt), "s"(g.deal), "s"(g.chunk), "s"(g.batch));
+    const TileCoord tc = tile_of(blockIdx.x & 7, blockIdx.x >> 3, g.mt, g.nt, g.chunk, g.deal, g.batch);
+    if (!tc.valid) return;
+    const int KB = g.kblocks;
+    const __amdgpu_buffer_rsrc_t rA = rows_rsrc(g.a + (size_t)tc.p * g.a_pstride, tc.ti * T::kTm, T::kABytes, KB);
+    const __amdgpu_buffer_rsrc_t rB = rows_rsrc(g.b + (size_t)tc.p * g.b_pstride, tc.tj * T::kTn, T::kBBytes, KB);
+
+    const int pre = KB < S ? KB : S;
+    for (int s = 0; s < pre; ++s)
+#pragma unroll
+        for (int q = 0; q < L; ++q) copy_part<T>(rA, rB, s, lds + s * T::kBuf, tid, wave, q);
+    sched_fence();
+    v4i acc[M][N];
+#pragma unroll
+    for (int i = 0; i < M; ++i)
+#pragma unroll
+        for (int j = 0; j < N; ++j) acc[i][j] = v4i{};
+#pragma unroll
+    for (int i = 0; i < M; ++i)
+#pragma unroll
+        for (int j = 0; j < N; ++j) asm volatile("" : "+a"(acc[i][j]));
+    asm volatile("s_nop 4");   // the fill before the first MFMA reads it (see acc_after_fill)
+    v4i f0[M + N], f1[M + N];
+    wait_stages<L>(pre - 1);
+    stage_barrier();
+#pragma unroll
+    for (int f = 0; f < M + N; ++f) f0[f] = frag_of<T>(lds, aoff, boff, lane, f);
+    wait_lds();
+
+    // Stage kb with its fragments in c: the next stage's are read into n and
+    // stage kb + S is copied into the buffer that stage kb leaves.
+    int buf = 0;   // kb % S
+    auto stage = [&](int kb, const v4i(&c)[M + N], v4i(&n)[M + N], int younger, bool next, bool refill, auto steady) {
+        constexpr bool STEADY = decltype(steady)::value;
+        constexpr int C = M * N, R = M + N;
+        if constexpr (STEADY) wait_vm<(S - 2) * L>();
+        else wait_stages<L>(younger);
+        stage_barrier();
+        const int nb = buf + 1 == S ? 0 : buf + 1;
+        const int8_t *nbuf = lds + nb * T::kBuf;
+        int8_t *rbuf = lds + buf * T::kBuf;
+#pragma unroll
+        for (int t = 0; t < C; ++t) {
+            const int i = t / N, j = (i & 1) ? N - 1 - t % N : t % N;
+            mfma(acc[i][j], c[i], c[M + j]);
+#pragma unroll
+            for (int f = 0; f < R; ++f)
+                if (f * C * 3 / (4 * R) == t && (STEADY || next)) n[f] = frag_of<T>(nbuf, aoff, boff, lane, f);
+#pragma unroll
+            for (int q = 0; q < L; ++q)
+                if ((2 * q + 1) * C / (2 * L) == t && (STEADY || refill)) copy_part<T>(rA, rB, kb + S, rbuf, tid, wave, q);
+        }
+        buf = nb;
+        wait_lds();
+    };
+    int kb = 0;
+    for (; kb + S + 1 < KB; kb += 2) {
+        stage(kb, f0, f1, 0, true, true, std::true_type());
+        stage(kb + 1, f1, f0, 0, true, true, std::true_type());
+    }
+    for (; kb < KB; kb += 2) {
+        stage(kb, f0, f1, min(KB - 1, kb + S - 1) - (kb + 1), kb + 1 < KB, kb + S < KB, std::false_type());
+        if (kb + 1 < KB)
+            stage(kb + 1, f1, f0, min(KB - 1, kb + S) - (kb + 2), kb + 2 < KB, kb + 1 + S < KB, std::false_type());
+    }
+
+    asm volatile("s_nop 7\n s_nop 7\n s_nop 7");   // the last MFMAs (see acc_after_mfma)
+#pragma unroll
+    for (int i = 0; i < M; ++i)
+#pragma unroll
+        for (int j = 0; j < N; ++j) asm volatile("" : "+a"(acc[i][j]));
+    int8_t *C = g.c + (size_t)tc.p * g.c_pstride + (size_t)(tc.tj * T::kTn + wc * N * 16 + (lane & 15)) * g.ldc +
+                tc.ti * T::kTm + wr * M * 16 + 16 * (lane >> 4);
+    store_blocks<M, N>(acc, C, g.ldc, g.mod[tc.p], g.inv[tc.p]);
+}
+
+typedef TileShape<2, 2, 8, 4, 3> Tile256x128;
+typedef TileShape<2, 2, 4, 4, 3> Tile128x128;
+typedef TileShape<1, 4, 4, 1, 5> Tile64x64;
+
+}  // namespace
+
+hipError_t plan_gemm(GemmArgs &ga, int rows, int cols) {
+    const GemmPlan p = gemm_plan(rows, cols, ga.kblocks, ga.batch, kStageBytes);
+    if (p.s.grid > 0x7FFFFFFF || p.s.slots >= (1L << kSlotBits)) return hipErrorInvalidValue;
+    ga.shape = p.shape;
+    ga.tm = p.tm;
+    ga.tn = p.tn;
+    ga.mt = p.mt;
+    ga.nt = p.nt;
+    ga.deal = p.s.deal;
+    ga.chunk = p.s.chunk;
+    ga.slots = (int)p.s.slots;
+    ga.fixed = (int)p.s.fixed;
+    ga.grid = p.s.grid;
+    return hipSuccess;
+}
+
+hipError_t launch_gemm(const GemmArgs &ga, hipStream_t st) {
     static_assert(kThreads * 16 * kLoadsPerStage == 2 * kStageBytes, "stage copy covers A and B");
-    GemmArgs ga = ga_in;
-    const GemmSchedule sc = gemm_plan(ga.mt, ga.nt, ga.kblocks, ga.batch, kStageBytes);
-    if (sc.grid == 0) return hipSuccess;
-    if (sc.grid > 0x7FFFFFFF || sc.slots >= (1L << kSlotBits)) return hipErrorInvalidValue;
-    ga.deal = sc.deal;
-    ga.chunk = sc.chunk;
-    ga.fixed = (int)sc.fixed;
-    ga.slots = (int)sc.slots;
-    const long grid = sc.grid;
-    gemm_i8_kernel<<<(unsigned)grid, kThreads, 0, st>>>(ga);
+    if (ga.grid <= 0) return hipSuccess;
+    const unsigned grid = (unsigned)ga.grid;
+    switch (ga.shape) {
+    case 0: gemm_i8_kernel<<<grid, kThreads, 0, st>>>(ga); break;
+    case 1: gemm_i8_multi<Tile256x128><<<grid, kThreads, 0, st>>>(ga); break;
+    case 2: gemm_i8_multi<Tile128x128><<<grid, kThreads, 0, st>>>(ga); break;
+    case 3: gemm_i8_multi<Tile64x64><<<grid, kThreads, 0, st>>>(ga); break;
+    default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 

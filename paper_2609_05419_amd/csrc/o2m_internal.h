@@ -176,10 +176,10 @@ hipError_t launch_exponents_direct(ElemType et, bool cs, const CsCombineArgs &g,
 struct PlaneGeom {
     int rows, k;         // logical sizes (SYRK: k = ceil(kreal / 2))
     int kreal;           // SYRK: columns of the real matrix
-    int rows_pad, kblocks;   // kblocks: k-blocks of this source
+    int rows_pad, kblocks;   // rows written (a multiple of 16); k-blocks of this source
     int plane_kblocks;       // k-blocks of the destination planes
     int kofs_p, kofs_m;      // k-block offsets in the + and - planes
-    size_t plane_bytes;  // rows_pad * plane_kblocks * 64
+    size_t plane_bytes;  // of a whole plane
     int conj;            // 1: the operand is conj(X) (a conjugate-transposed GEMM operand)
 };
 // One operand of a residue launch.
@@ -220,20 +220,25 @@ struct GemmArgs {
     const int8_t *b;
     int8_t *c;
     size_t a_pstride, b_pstride, c_pstride;  // bytes between consecutive batch items
-    int mt, nt, kblocks;                     // tiles along m, n; k stages
+    int kblocks;                             // k stages
+    int shape, tm, tn;                       // tile shape (plan_gemm sets this and the next four lines)
+    int mt, nt;                              // tiles along m, n
+    int chunk, deal;                         // tile order (tile_schedule.h)
+    int slots, fixed;                        // slots per XCD; of those taken by workgroup index
+    long grid;                               // workgroups
     int batch;
     int ldc;
-    int chunk, deal;                         // tile order (tile_schedule.h; set by the launcher)
-    int slots;                               // slots per XCD (launcher)
-    int fixed;                               // slots per XCD taken by workgroup index (launcher)
     unsigned *queue;                         // 8 pool counters, one per XCD, kQueueStride
                                              // apart; zero at launch
     int mod[kMaxProducts];
     double inv[kMaxProducts];
 };
+// Chooses the tile shape and schedule for rows x cols outputs per product
+// (kblocks and batch are set).  Operand rows are read up to the next multiple
+// of tm (A) and tn (B).
+hipError_t plan_gemm(GemmArgs &ga, int rows, int cols);
+// fixed < slots: the launch claims slots at run time, and its queue must be zero.
 hipError_t launch_gemm(const GemmArgs &ga, hipStream_t st);
-// Whether that launch claims slots at run time: then its queue must be zero.
-bool gemm_uses_queue(const GemmArgs &ga);
 
 // K4: CRT + lift + descale.
 //   mode 0 ZGEMM  (planes 2l = C+, 2l+1 = C-), output complex

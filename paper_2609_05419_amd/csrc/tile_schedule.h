@@ -129,17 +129,90 @@ O2M_HD inline GemmSchedule gemm_schedule(int mt, int nt, int kblocks, int batch,
     return s;
 }
 
-// The schedule a launch uses: spread below 8 windows per product (a single
-// tile-row or tile-column: below one tile per XCD), otherwise gemm_schedule.
-O2M_HD inline GemmSchedule gemm_plan(int mt, int nt, int kblocks, int batch, long stage_bytes) {
-    const long tiles = (long)mt * nt;
-    if (tiles <= 0 || batch <= 0 || kblocks <= 0 || tiles >= (mt > 1 && nt > 1 ? kXcds * kWindowTiles : kXcds))
-        return gemm_schedule(mt, nt, kblocks, batch, stage_bytes);
-    GemmSchedule s = {kSpread, 0, 0, 0, 0};
-    s.slots = (tiles * batch + kXcds - 1) / kXcds;
-    s.chunk = (int)s.slots;
-    pool_slots(s, kblocks);
-    return s;
+// Tile shapes of the GEMM kernels: output rows and columns of a workgroup, and
+// workgroups a CU holds.  The time of a launch is estimated as
+//   launch + rounds (tile + stage KB) + latency KB   [us]
+// over its KB k-stages, rounds = tiles per CU / workgroups per CU, tiles per
+// CU rounded up: `tile` is a tile's prologue and epilogue, `stage` a stage
+// with the CU full, `latency` what a stage costs however empty the CU is.  The
+// constants fit the GEMM phase of 30 shapes from 60^3 to 4096^3 measured with
+// each of the four (to 8-11%); the estimate's choice is the fastest or within
+// 7% of it on all of them.  Large products take the 256 x 256 tile, which
+// moves the least data per MFMA (2048^3: 230 us against 241, 271 and 447);
+// short k, ragged sizes and products of fewer tiles than CUs the smaller ones
+// (700^3: 34.0, 27.7, 25.2, 28.5; 96 x 80 x 200: 13.0, 10.6, 8.6, 7.2;
+// 4096 x 96 x 4096: 129, 113, 116, 163).
+struct GemmShape {
+    int tm, tn, per_cu;
+    double launch, tile, stage, latency;
+};
+constexpr int kCus = 256;
+constexpr int kGemmShapes = 4;
+O2M_HD inline GemmShape gemm_shape_of(int i) {
+    constexpr GemmShape shapes[kGemmShapes] = {
+        {256, 256, 1, 4.0, 6.2, 0.684, 0.0},
+        {256, 128, 2, 6.4, 4.75, 0.749, 0.091},
+        {128, 128, 3, 6.35, 3.2, 0.662, 0.133},
+        {64, 64, 4, 6.4, 1.83, 0.359, 0.077},
+    };
+    return shapes[i];
+}
+
+O2M_HD inline double gemm_estimate(const GemmShape &s, long rows, long cols, int kblocks, int batch) {
+    const long tiles = (rows + s.tm - 1) / s.tm * ((cols + s.tn - 1) / s.tn) * batch;
+    const double rounds = (double)((tiles + kCus - 1) / kCus) / s.per_cu;
+    return s.launch + rounds * (s.tile + s.stage * kblocks) + s.latency * kblocks;
+}
+
+// The launch of one batched int8 GEMM: tile shape, tiles and schedule.
+struct GemmPlan {
+    int shape, tm, tn;
+    int mt, nt;
+    GemmSchedule s;
+};
+
+// rows x cols outputs per product, kblocks k-stages of stage_bytes per
+// 256-row operand tile, batch products.  A 256 x 256 launch is spread below 8
+// windows per product (a single tile-row or tile-column: below one tile per
+// XCD) and follows gemm_schedule otherwise; the smaller tiles, of which an XCD
+// holds per_cu windows, are spread below 8 of these and never pooled.
+O2M_HD inline GemmPlan gemm_plan(int rows, int cols, int kblocks, int batch, long stage_bytes) {
+    GemmPlan p = {0, 0, 0, 0, 0, {0, 0, 0, 0, 0}};
+    if (rows <= 0 || cols <= 0 || batch <= 0 || kblocks <= 0) return p;
+    double best = 0.0;
+    for (int i = 0; i < kGemmShapes; ++i) {
+        const double t = gemm_estimate(gemm_shape_of(i), rows, cols, kblocks, batch);
+        if (i == 0 || t < best) {
+            best = t;
+            p.shape = i;
+        }
+    }
+    const GemmShape sh = gemm_shape_of(p.shape);
+    p.tm = sh.tm;
+    p.tn = sh.tn;
+    p.mt = (rows - 1) / sh.tm + 1;
+    p.nt = (cols - 1) / sh.tn + 1;
+    const long tiles = (long)p.mt * p.nt;
+    const bool narrow = p.shape == 0 && (p.mt == 1 || p.nt == 1);
+    const bool spread = tiles < (narrow ? kXcds : (long)kXcds * kWindowTiles * sh.per_cu);
+    if (spread) {
+        p.s.deal = kSpread;
+        p.s.slots = (tiles * batch + kXcds - 1) / kXcds;
+        p.s.chunk = (int)p.s.slots;
+    } else if (p.shape == 0) {
+        p.s = gemm_schedule(p.mt, p.nt, kblocks, batch, stage_bytes);
+        return p;
+    } else {
+        p.s.chunk = (int)((tiles + kXcds - 1) / kXcds);
+        p.s.slots = (long)p.s.chunk * batch;
+    }
+    if (p.shape == 0) {
+        pool_slots(p.s, kblocks);
+    } else {
+        p.s.fixed = p.s.slots;
+        p.s.grid = kXcds * p.s.slots;
+    }
+    return p;
 }
 
 }  // namespace o2m

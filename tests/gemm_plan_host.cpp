@@ -3,14 +3,14 @@
 #include "../paper_2609_05419_amd/csrc/tile_schedule.h"
 
 extern "C" {
-// deal, chunk, slots, fixed, grid
-void t_plan(int mt, int nt, int kblocks, int batch, long stage_bytes, long *out) {
-    const o2m::GemmSchedule s = o2m::gemm_plan(mt, nt, kblocks, batch, stage_bytes);
-    out[0] = s.deal;
-    out[1] = s.chunk;
-    out[2] = s.slots;
-    out[3] = s.fixed;
-    out[4] = s.grid;
+// shape, tm, tn, mt, nt, deal, chunk, slots, fixed, grid
+void t_plan(int rows, int cols, int kblocks, int batch, long stage_bytes, long *out) {
+    const o2m::GemmPlan p = o2m::gemm_plan(rows, cols, kblocks, batch, stage_bytes);
+    const long v[10] = {p.shape, p.tm, p.tn, p.mt, p.nt, p.s.deal, p.s.chunk, p.s.slots, p.s.fixed, p.s.grid};
+    for (int i = 0; i < 10; ++i) out[i] = v[i];
+}
+double t_estimate(int shape, int rows, int cols, int kblocks, int batch) {
+    return o2m::gemm_estimate(o2m::gemm_shape_of(shape), rows, cols, kblocks, batch);
 }
 // tiles[4 * (x * slots + slot) + {valid, p, ti, tj}]
 void t_plan_tiles(int mt, int nt, int chunk, int deal, int batch, long slots, int *tiles) {

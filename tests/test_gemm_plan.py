@@ -1,7 +1,7 @@
-"""Host build of the int8 GEMM's launch plan (tile_schedule.h, gemm_plan): on
-both sides of the line between the spread layout and the product-major one,
-every tile of every product has exactly one slot, and spread slots keep an
-XCD's tiles in consecutive places of the sequence."""
+"""Host build of the int8 GEMM's launch plan (tile_schedule.h, gemm_plan):
+whichever tile shape and layout it takes, every tile of every product has
+exactly one slot, the tiles cover the outputs, and an XCD's spread slots are
+consecutive places of the sequence of tiles."""
 import ctypes
 import os
 import subprocess
@@ -9,8 +9,11 @@ import subprocess
 import numpy as np
 import pytest
 
+from gemm_shapes import SHAPES
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 STAGE_BYTES = 256 * 64
+PER_CU = {0: 1, 1: 2, 2: 3, 3: 4}
 
 
 @pytest.fixture(scope="module")
@@ -21,32 +24,54 @@ def lib(tmp_path_factory):
     L = ctypes.CDLL(str(out))
     I, Lg, P = ctypes.c_int, ctypes.c_long, ctypes.c_void_p
     L.t_plan.argtypes = [I, I, I, I, Lg, P]
+    L.t_estimate.argtypes = [I, I, I, I, I]
+    L.t_estimate.restype = ctypes.c_double
     L.t_plan_tiles.argtypes = [I, I, I, I, I, Lg, P]
     return L
 
 
-@pytest.mark.parametrize("mt,nt,kb,batch", [
-    (1, 1, 1, 1), (1, 1, 4, 32), (2, 2, 13, 32), (4, 4, 16, 32), (7, 6, 33, 16), (8, 8, 32, 32), (12, 12, 40, 16),
-    (7, 1, 5, 32), (1, 8, 5, 32), (16, 1, 64, 32), (2, 127, 3, 74), (15, 17, 64, 5), (16, 16, 64, 16), (17, 16, 64, 16),
-    (8, 8, 129, 32),                      # spread and pooled
-    (0, 4, 4, 4), (4, 4, 0, 4)])
-def test_plan_covers_every_tile_once(lib, mt, nt, kb, batch):
-    out = np.zeros(5, dtype=np.int64)
-    lib.t_plan(mt, nt, kb, batch, STAGE_BYTES, out.ctypes.data)
-    deal, chunk, slots, fixed, grid = (int(v) for v in out)
-    if mt * nt * kb * batch == 0:
-        assert grid == 0
-        return
-    assert (deal == 2) == (mt * nt < (256 if min(mt, nt) > 1 else 8))
+def plan(lib, rows, cols, kb, batch):
+    out = np.zeros(10, dtype=np.int64)
+    lib.t_plan(rows, cols, kb, batch, STAGE_BYTES, out.ctypes.data)
+    return dict(zip(("shape", "tm", "tn", "mt", "nt", "deal", "chunk", "slots", "fixed", "grid"), (int(v) for v in out)))
+
+
+CASES = [(1, 1, 1, 1), (96, 80, 4, 32), (500, 333, 13, 32), (1024, 1024, 16, 32), (1537, 1283, 33, 16),
+         (2048, 2048, 32, 32), (3001, 3001, 40, 16), (4096, 96, 64, 32), (96, 4096, 64, 32), (4096, 4096, 64, 16),
+         (2047, 2049, 129, 32),               # spread and pooled
+         (8192, 8192, 128, 32), (5632, 5888, 375, 32), (16384, 33, 1, 74), (20000, 20000, 1, 64),
+         (33, 20000, 2000, 2)]
+
+
+@pytest.mark.parametrize("rows,cols,kb,batch", CASES)
+def test_plan_covers_every_tile_once(lib, rows, cols, kb, batch):
+    p = plan(lib, rows, cols, kb, batch)
+    mt, nt, slots = p["mt"], p["nt"], p["slots"]
+    assert (mt - 1) * p["tm"] < rows <= mt * p["tm"] and (nt - 1) * p["tn"] < cols <= nt * p["tn"]
+    est = [lib.t_estimate(i, rows, cols, kb, batch) for i in range(4)]
+    assert est[p["shape"]] == min(est)
     t = np.zeros((8, slots, 4), dtype=np.int32)
-    lib.t_plan_tiles(mt, nt, chunk, deal, batch, slots, t.ctypes.data)
-    keys = [tuple(k[1:]) for k in t.reshape(-1, 4) if k[0]]
-    assert len(keys) == len(set(keys)) == mt * nt * batch
-    assert all(0 <= p < batch and 0 <= i < mt and 0 <= j < nt for p, i, j in keys)
-    pool = slots // 8 if kb >= 128 and slots >= 256 else 0
-    assert slots - fixed == pool and grid == 8 * (slots + (-(-slots // 12) if pool else 0))
-    if deal == 2:
-        assert slots == -(-mt * nt * batch // 8)
+    lib.t_plan_tiles(mt, nt, p["chunk"], p["deal"], batch, slots, t.ctypes.data)
+    keys = t[t[..., 0].astype(bool)][:, 1:].astype(np.int64)
+    assert (keys >= 0).all() and (keys < [batch, mt, nt]).all()
+    flat = (keys[:, 0] * mt + keys[:, 1]) * nt + keys[:, 2]
+    assert len(flat) == len(np.unique(flat)) == mt * nt * batch
+    pool = slots // 8 if p["shape"] == 0 and kb >= 128 and slots >= 256 else 0
+    assert slots - p["fixed"] == pool and p["grid"] == 8 * (slots + (-(-slots // 12) if pool else 0))
+    narrow = p["shape"] == 0 and min(mt, nt) == 1
+    assert (p["deal"] == 2) == (mt * nt < (8 if narrow else 256 * PER_CU[p["shape"]]))
+    if p["deal"] == 2:
         # product-major over the XCDs in turn: the sequence of products never falls
-        p = t[..., 1][t[..., 0].astype(bool)]
-        assert (np.diff(p) >= 0).all()
+        assert slots == -(-mt * nt * batch // 8) and (np.diff(keys[:, 0]) >= 0).all()
+
+
+def test_empty_problem(lib):
+    for c in [(0, 4, 4, 4), (4, 0, 4, 4), (4, 4, 0, 4), (4, 4, 4, 0)]:
+        assert plan(lib, *c)["grid"] == 0
+
+
+def test_sizes_take_their_shapes(lib):
+    """The sizes that the GPU test runs reach every kernel."""
+    for shape, sizes in SHAPES.items():
+        for rows, cols, k, batch in sizes:
+            assert plan(lib, rows, cols, -(-k // 64), batch)["shape"] == shape, (rows, cols, k, batch)

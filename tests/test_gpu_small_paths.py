@@ -203,3 +203,36 @@ def test_gauss_maxima(o2m, m, n, k):
     assert o2m.get_status() == 0 and np.array_equal(got, O.gauss_4m(A, B))
     o2m.gauss_gemm_2m(dA, dB, n_moduli=2)                # M = 56153: the bound is far exceeded
     assert o2m.get_status() == o2m.STATUS_OVERFLOW
+
+
+# ------------------------------------------------------------------ GEMM tiles
+def _gemm_sizes():
+    from gemm_shapes import SHAPES
+    return [(s, *c) for s, cs in SHAPES.items() for c in cs]
+
+
+@pytest.mark.parametrize("shape,m,n,k,products", _gemm_sizes())
+def test_gemm_tile_shapes(o2m, shape, m, n, k, products):
+    """Every tile shape of the int8 GEMM (test_gemm_plan checks that these
+    sizes take it): two entries of every 64 x 64 block and the corners."""
+    N = 32 if products == 74 else products // 2
+    a, b = W.complex_matrix(m, k, 31, dist="phi", phi=0.5), W.complex_matrix(k, n, 32, dist="phi", phi=0.5)
+    got = host(o2m.zgemm_2m(to_dev(a), to_dev(b), n_moduli=N))
+    rng = np.random.default_rng(m + n)
+    ent = [(i, j) for i in (0, m - 1) for j in (0, n - 1)]
+    for i in range(0, m, 64):
+        for j in range(0, n, 64):
+            ent += [(int(rng.integers(i, min(m, i + 64))), int(rng.integers(j, min(n, j + 64)))) for _ in range(2)]
+    assert same_bits(np.array([got[i, j] for i, j in ent]), O.oq_zgemm(a, b, N, entries=ent))
+
+
+@pytest.mark.parametrize("n,k", [(65, 100), (130, 70), (190, 600), (700, 900), (1000, 65)])
+def test_gemm_tiles_symmetric(o2m, n, k):
+    """The symmetric calls read both operands from one set of planes, written
+    up to whole tiles of either side."""
+    a = W.complex_matrix(n, k, 33, dist="phi", phi=0.5)
+    got = host(o2m.zherk_2m(to_dev(a)))
+    rng = np.random.default_rng(n)
+    ent = [(i, j) for i in (0, n - 1) for j in (0, n - 1) if i >= j]
+    ent += [(max(i, j), min(i, j)) for i, j in rng.integers(0, n, (400, 2)).tolist()]
+    assert same_bits(np.array([got[i, j] for i, j in ent]), O.oq_zherk(a, 16, entries=ent))
