@@ -170,6 +170,11 @@ __device__ inline void mfma(v4i &acc, const v4i &a, const v4i &b) {
     asm volatile("v_mfma_i32_16x16x64_i8 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b) : "memory");
 }
 
+// acc = a b^T: the first MFMA of a block, in place of a zero fill.
+__device__ inline void mfma_first(v4i &acc, const v4i &a, const v4i &b) {
+    asm volatile("v_mfma_i32_16x16x64_i8 %0, %1, %2, 0" : "=a"(acc) : "v"(a), "v"(b) : "memory");
+}
+
 // Wait states between the accumulator registers' last writer and their next
 // reader.  Each asm takes a row of accumulators as operands, so no access to
 // them can move across it.
@@ -295,7 +300,7 @@ __device__ inline void prologue_wait(const Wave &w, int KB, v4i (&fa)[8], v4i (&
 // the fragment reads of stage kb+1 into (na, nb) and, if `refill`, the copy of
 // stage kb+4 of (rA, rB) into the freed buffer, both issued first.  Used for
 // the last stages of a tile, where waits shrink.
-__device__ inline void edge_stage(v4i (&acc)[8][8], const Wave &w, int kb, const v4i (&ca)[8], const v4i (&cb)[8],
+__device__ inline void edge_stage(v4i (&acc)[8][8], const Wave &w, int kb, int sstage, const v4i (&ca)[8], const v4i (&cb)[8],
                                   v4i (&na)[8], v4i (&nb)[8], int younger, bool next, bool refill,
                                   __amdgpu_buffer_rsrc_t rA, __amdgpu_buffer_rsrc_t rB) {
     if (younger >= 2) wait_vm<2 * kLoadsPerStage>();
@@ -310,7 +315,7 @@ __device__ inline void edge_stage(v4i (&acc)[8][8], const Wave &w, int kb, const
             nb[f] = read_frag(nbuf, w.aoff, w.boff, w.lane, 8 + f);
         }
     }
-    if (refill) load_stage(rA, rB, kb + kStages, w.lds + (kb % kStages) * kStageBuf, w.tid, w.wave);
+    if (refill) load_stage(rA, rB, sstage, w.lds + (kb % kStages) * kStageBuf, w.tid, w.wave);
 #pragma unroll
     for (int i = 0; i < 8; ++i)
 #pragma unroll
@@ -325,10 +330,11 @@ __device__ inline void edge_stage(v4i (&acc)[8][8], const Wave &w, int kb, const
 // blocks boustrophedon, so that each shares an operand fragment with the one
 // before it: the launch is held by its power draw, and the operand registers
 // toggle less (8192^3 N = 16: 11.51 -> 11.46 ms, smaller shapes level).
+template <bool FIRST = false>
 __device__ inline void steady_stage(v4i (&acc)[8][8], const Wave &w, int kb, const v4i (&ca)[8], const v4i (&cb)[8],
                                     v4i (&na)[8], v4i (&nb)[8], __amdgpu_buffer_rsrc_t sA,
-                                    __amdgpu_buffer_rsrc_t sB, int sstage) {
-    wait_vm<2 * kLoadsPerStage>();
+                                    __amdgpu_buffer_rsrc_t sB, int sstage, bool landed = false) {
+    if (!landed) wait_vm<2 * kLoadsPerStage>();
     stage_barrier();
     const int8_t *nbuf = w.lds + ((kb + 1) % kStages) * kStageBuf;
     int8_t *rbuf = w.lds + (kb % kStages) * kStageBuf;
@@ -337,7 +343,8 @@ __device__ inline void steady_stage(v4i (&acc)[8][8], const Wave &w, int kb, con
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const int jj = (i & 1) ? 7 - j : j;
-            mfma(acc[i][jj], ca[i], cb[jj]);
+            if (FIRST) mfma_first(acc[i][jj], ca[i], cb[jj]);
+            else mfma(acc[i][jj], ca[i], cb[jj]);
             const int t = 8 * i + j;
             if (t < 32 && (t & 1) == 0) {
                 const int f = t >> 1;
@@ -350,12 +357,12 @@ __device__ inline void steady_stage(v4i (&acc)[8][8], const Wave &w, int kb, con
 }
 
 // The tile's output block for this wave: C mod m as int8.
-__device__ inline void epilogue(v4i (&acc)[8][8], const Wave &w, const GemmArgs &g, const TileCoord &tc) {
+__device__ inline void epilogue(v4i (&acc)[8][8], const Wave &w, const GemmArgs &g, int p, int ti, int tj) {
     acc_after_mfma(acc);
     const int wr = w.wave >> 1, wc = w.wave & 1;
-    int8_t *C = g.c + (size_t)tc.p * g.c_pstride + (size_t)(tc.tj * 256 + wc * 128 + (w.lane & 15)) * g.ldc +
-                tc.ti * 256 + wr * 128 + 16 * (w.lane >> 4);
-    store_blocks<8, 8>(acc, C, g.ldc, g.mod[tc.p], g.inv[tc.p]);
+    int8_t *C = g.c + (size_t)p * g.c_pstride + (size_t)(tj * 256 + wc * 128 + (w.lane & 15)) * g.ldc +
+                ti * 256 + wr * 128 + 16 * (w.lane >> 4);
+    store_blocks<8, 8>(acc, C, g.ldc, g.mod[p], g.inv[p]);
 }
 
 __device__ inline __amdgpu_buffer_rsrc_t rsrc_a(const GemmArgs &g, const TileCoord &tc) {
@@ -419,7 +426,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_i8_kernel(GemmArgs g) {
     }
     auto tail = [&](v4i (&ca)[8], v4i (&cb)[8], v4i (&na)[8], v4i (&nb)[8]) {
         if (kb < KB) {
-            edge_stage(acc, w, kb, ca, cb, na, nb, min(KB - 1, kb + kStages - 1) - (kb + 1), kb + 1 < KB,
+            edge_stage(acc, w, kb, kb + kStages, ca, cb, na, nb, min(KB - 1, kb + kStages - 1) - (kb + 1), kb + 1 < KB,
                        kb + kStages < KB, rA, rB);
             ++kb;
         }
@@ -430,7 +437,86 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_i8_kernel(GemmArgs g) {
     tail(fa1, fb1, fa0, fb0);
     tail(fa0, fb0, fa1, fb1);
 
-    epilogue(acc, w, g, tc);
+    epilogue(acc, w, g, tc.p, tc.ti, tc.tj);
+}
+
+// Several output tiles per workgroup, one after another: slots blockIdx.x / 8,
+// + kResident, .. of its XCD (gemm_plan chooses when).  The last four stages of
+// a tile refill the ring with the next tile's first four, which land during
+// the epilogue, so that only the first tile waits for its operands (7k of the
+// 52k cycles of a 2048^3 tile), and a tile's first stage takes a zero addend
+// in place of a fill (1k).  Stage waits count copies: after an epilogue its 16
+// stores per wave are the youngest of the counter, so the wait of stage 0 for
+// all but 16 leaves them in flight and has seen stages 1 to 3 land; stages 1
+// and 2 (`calm`) need no wait of their own, and from stage 3 on the stores are
+// the oldest.
+__global__ __launch_bounds__(kThreads, 1) void gemm_i8_chain(GemmArgs g) {
+    __shared__ __attribute__((aligned(1024))) int8_t lds[kPipeBytes];
+    const Wave w = wave_of(lds);
+    asm volatile("" ::"s"(g.a), "s"(g.b), "s"(g.a_pstride), "s"(g.b_pstride), "s"(g.kblocks), "s"(g.mt),
+                 "s"(g.nt), "s"(g.deal), "s"(g.chunk), "s"(g.batch), "s"(g.slots));
+    const int x = blockIdx.x & 7, KB = g.kblocks;
+    int slot = blockIdx.x >> 3;
+    TileCoord nt;
+    static_assert(kStages == 4, "the last tile ends in four edge stages; kChainMin = kStages + 1");
+    // the next slot of this workgroup that holds a tile (nt), from `slot` on
+    auto advance = [&]() {
+        for (; slot < g.slots; slot += kResident) {
+            nt = tile_of(x, slot, g.mt, g.nt, g.chunk, g.deal, g.batch);
+            if (nt.valid) return true;
+        }
+        return false;
+    };
+    if (!advance()) return;   // whole workgroup: no barrier is pending
+    int p = nt.p, ti = nt.ti, tj = nt.tj;
+    __amdgpu_buffer_rsrc_t rA = rsrc_a(g, nt), rB = rsrc_b(g, nt);
+    prologue_copies(w, rA, rB, KB);
+    v4i acc[8][8];
+    v4i fa0[8], fb0[8], fa1[8], fb1[8];
+    prologue_wait(w, KB, fa0, fb0);
+    int base = 0;         // ring position of the tile's stage 0
+    int calm = 0;         // stages of the tile whose successors had landed before it began (1..calm)
+    for (;;) {
+        slot += kResident;
+        const bool more = advance();
+        const __amdgpu_buffer_rsrc_t nA = more ? rsrc_a(g, nt) : rA, nB = more ? rsrc_b(g, nt) : rB;
+        const int steady = more ? KB : KB - kStages;   // the rest is the launch's last four stages
+        auto stage = [&](int kb, auto first, v4i(&ca)[8], v4i(&cb)[8], v4i(&na)[8], v4i(&nb)[8]) {
+            const bool own = kb + kStages < KB;      // the refill is this tile's
+            steady_stage<decltype(first)::value>(acc, w, base + kb, ca, cb, na, nb, own ? rA : nA, own ? rB : nB,
+                                                 own ? kb + kStages : kb + kStages - KB, kb >= 1 && kb <= calm);
+        };
+        stage(0, std::true_type(), fa0, fb0, fa1, fb1);
+        int kb = 1;
+        for (; kb + 1 < steady; kb += 2) {
+            stage(kb, std::false_type(), fa1, fb1, fa0, fb0);
+            stage(kb + 1, std::false_type(), fa0, fb0, fa1, fb1);
+        }
+        if (kb < steady) {
+            stage(kb, std::false_type(), fa1, fb1, fa0, fb0);
+        } else {
+#pragma unroll
+            for (int f = 0; f < 8; ++f) {
+                fa0[f] = fa1[f];
+                fb0[f] = fb1[f];
+            }
+        }
+        if (!more) break;
+        epilogue(acc, w, g, p, ti, tj);
+        base = (base + KB) % kStages;
+        p = nt.p;
+        ti = nt.ti;
+        tj = nt.tj;
+        rA = nA;
+        rB = nB;
+        calm = 2;
+    }
+    const int kb = base + KB - kStages;
+    edge_stage(acc, w, kb, 0, fa0, fb0, fa1, fb1, 2, true, false, rA, rB);
+    edge_stage(acc, w, kb + 1, 0, fa1, fb1, fa0, fb0, 1, true, false, rA, rB);
+    edge_stage(acc, w, kb + 2, 0, fa0, fb0, fa1, fb1, 0, true, false, rA, rB);
+    edge_stage(acc, w, kb + 3, 0, fa1, fb1, fa0, fb0, 0, false, false, rA, rB);
+    epilogue(acc, w, g, p, ti, tj);
 }
 
 // ---- smaller tiles, several workgroups per CU ------------------------------
@@ -586,6 +672,7 @@ hipError_t plan_gemm(GemmArgs &ga, int rows, int cols) {
     const GemmPlan p = gemm_plan(rows, cols, ga.kblocks, ga.batch, kStageBytes);
     if (p.s.grid > 0x7FFFFFFF || p.s.slots >= (1L << kSlotBits)) return hipErrorInvalidValue;
     ga.shape = p.shape;
+    ga.chain = p.chain;
     ga.tm = p.tm;
     ga.tn = p.tn;
     ga.mt = p.mt;
@@ -603,7 +690,10 @@ hipError_t launch_gemm(const GemmArgs &ga, hipStream_t st) {
     if (ga.grid <= 0) return hipSuccess;
     const unsigned grid = (unsigned)ga.grid;
     switch (ga.shape) {
-    case 0: gemm_i8_kernel<<<grid, kThreads, 0, st>>>(ga); break;
+    case 0:
+        if (ga.chain) gemm_i8_chain<<<grid, kThreads, 0, st>>>(ga);
+        else gemm_i8_kernel<<<grid, kThreads, 0, st>>>(ga);
+        break;
     case 1: gemm_i8_multi<Tile256x128><<<grid, kThreads, 0, st>>>(ga); break;
     case 2: gemm_i8_multi<Tile128x128><<<grid, kThreads, 0, st>>>(ga); break;
     case 3: gemm_i8_multi<Tile64x64><<<grid, kThreads, 0, st>>>(ga); break;

@@ -221,7 +221,8 @@ struct GemmArgs {
     int8_t *c;
     size_t a_pstride, b_pstride, c_pstride;  // bytes between consecutive batch items
     int kblocks;                             // k stages
-    int shape, tm, tn;                       // tile shape (plan_gemm sets this and the next four lines)
+    int shape, tm, tn;                       // tile shape (plan_gemm sets this and the next five lines)
+    int chain;                               // several tiles per workgroup
     int mt, nt;                              // tiles along m, n
     int chunk, deal;                         // tile order (tile_schedule.h)
     int slots, fixed;                        // slots per XCD; of those taken by workgroup index

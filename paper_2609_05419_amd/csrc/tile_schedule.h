@@ -168,8 +168,21 @@ O2M_HD inline double gemm_estimate(const GemmShape &s, long rows, long cols, int
 struct GemmPlan {
     int shape, tm, tn;
     int mt, nt;
+    int chain;       // 1: each workgroup takes every kResident-th slot of its XCD in turn
     GemmSchedule s;
 };
+
+// Chained launches of the 256 x 256 tile: one workgroup per CU takes its tiles
+// one after another, the next one's first stages on their way during the last
+// stages and the epilogue of the one before (measured, GEMM phase: 2048^3 234
+// -> 217 us, 4096 x 4096 x 2048 962 -> 877, 1024^3 44.0 -> 40.2, DSYRK 3001 x
+// 4999 305 -> 286).  With long k the prologue is a small part of a tile and the
+// workgroups of an XCD, which no dispatch lines up again, drift out of the L2
+// reuse of their strips: level to 0.5% slower at 64 stages (ZHERK 4096, 4096^3),
+// 1024 x 1024 x 65536 1412 -> 1487.
+// The ring of four stages needs five.
+constexpr int kResident = 32;    // workgroups per XCD
+constexpr int kChainMin = 5, kChainMax = 48;
 
 // rows x cols outputs per product, kblocks k-stages of stage_bytes per
 // 256-row operand tile, batch products.  A 256 x 256 launch is spread below 8
@@ -177,7 +190,7 @@ struct GemmPlan {
 // XCD) and follows gemm_schedule otherwise; the smaller tiles, of which an XCD
 // holds per_cu windows, are spread below 8 of these and never pooled.
 O2M_HD inline GemmPlan gemm_plan(int rows, int cols, int kblocks, int batch, long stage_bytes) {
-    GemmPlan p = {0, 0, 0, 0, 0, {0, 0, 0, 0, 0}};
+    GemmPlan p = {0, 0, 0, 0, 0, 0, {0, 0, 0, 0, 0}};
     if (rows <= 0 || cols <= 0 || batch <= 0 || kblocks <= 0) return p;
     double best = 0.0;
     for (int i = 0; i < kGemmShapes; ++i) {
@@ -195,22 +208,19 @@ O2M_HD inline GemmPlan gemm_plan(int rows, int cols, int kblocks, int batch, lon
     const long tiles = (long)p.mt * p.nt;
     const bool narrow = p.shape == 0 && (p.mt == 1 || p.nt == 1);
     const bool spread = tiles < (narrow ? kXcds : (long)kXcds * kWindowTiles * sh.per_cu);
-    if (spread) {
-        p.s.deal = kSpread;
-        p.s.slots = (tiles * batch + kXcds - 1) / kXcds;
-        p.s.chunk = (int)p.s.slots;
-    } else if (p.shape == 0) {
+    if (!spread && p.shape == 0) {
         p.s = gemm_schedule(p.mt, p.nt, kblocks, batch, stage_bytes);
-        return p;
     } else {
-        p.s.chunk = (int)((tiles + kXcds - 1) / kXcds);
-        p.s.slots = (long)p.s.chunk * batch;
-    }
-    if (p.shape == 0) {
-        pool_slots(p.s, kblocks);
-    } else {
+        p.s.deal = spread ? kSpread : 0;
+        p.s.chunk = (int)(((spread ? tiles * batch : tiles) + kXcds - 1) / kXcds);
+        p.s.slots = spread ? p.s.chunk : (long)p.s.chunk * batch;
         p.s.fixed = p.s.slots;
         p.s.grid = kXcds * p.s.slots;
+        if (p.shape == 0) pool_slots(p.s, kblocks);
+    }
+    if (p.shape == 0 && kblocks >= kChainMin && kblocks <= kChainMax && p.s.slots > kResident) {
+        p.chain = 1;   // (never pooled: that takes 128 stages)
+        p.s.grid = kXcds * kResident;
     }
     return p;
 }

@@ -3,11 +3,11 @@
 #include "../paper_2609_05419_amd/csrc/tile_schedule.h"
 
 extern "C" {
-// shape, tm, tn, mt, nt, deal, chunk, slots, fixed, grid
+// shape, tm, tn, mt, nt, deal, chunk, slots, fixed, grid, chain
 void t_plan(int rows, int cols, int kblocks, int batch, long stage_bytes, long *out) {
     const o2m::GemmPlan p = o2m::gemm_plan(rows, cols, kblocks, batch, stage_bytes);
-    const long v[10] = {p.shape, p.tm, p.tn, p.mt, p.nt, p.s.deal, p.s.chunk, p.s.slots, p.s.fixed, p.s.grid};
-    for (int i = 0; i < 10; ++i) out[i] = v[i];
+    const long v[11] = {p.shape, p.tm, p.tn, p.mt, p.nt, p.s.deal, p.s.chunk, p.s.slots, p.s.fixed, p.s.grid, p.chain};
+    for (int i = 0; i < 11; ++i) out[i] = v[i];
 }
 double t_estimate(int shape, int rows, int cols, int kblocks, int batch) {
     return o2m::gemm_estimate(o2m::gemm_shape_of(shape), rows, cols, kblocks, batch);

@@ -13,3 +13,9 @@ SHAPES = {
     0: [(783, 770, 64, 16), (772, 784, 128, 16), (387, 794, 256, 32), (389, 773, 320, 32), (719, 259, 448, 32),
         (1537, 130, 300, 32)],
 }
+
+# sizes of the 256 x 256 tile with several tiles per workgroup: from the fewest
+# k-stages up, even and odd counts, with idle slots and without, a second tile
+# for some workgroups only
+CHAINED = [(201, 4141, 320, 14), (206, 4279, 380, 14), (4134, 202, 440, 14), (203, 4146, 512, 14), (1801, 390, 448, 32),
+           (387, 645, 760, 74), (3497, 388, 570, 14), (273, 3885, 3050, 14)]

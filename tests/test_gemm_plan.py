@@ -9,7 +9,7 @@ import subprocess
 import numpy as np
 import pytest
 
-from gemm_shapes import SHAPES
+from gemm_shapes import CHAINED, SHAPES
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 STAGE_BYTES = 256 * 64
@@ -31,9 +31,9 @@ def lib(tmp_path_factory):
 
 
 def plan(lib, rows, cols, kb, batch):
-    out = np.zeros(10, dtype=np.int64)
+    out = np.zeros(11, dtype=np.int64)
     lib.t_plan(rows, cols, kb, batch, STAGE_BYTES, out.ctypes.data)
-    return dict(zip(("shape", "tm", "tn", "mt", "nt", "deal", "chunk", "slots", "fixed", "grid"), (int(v) for v in out)))
+    return dict(zip(("shape", "tm", "tn", "mt", "nt", "deal", "chunk", "slots", "fixed", "grid", "chain"), (int(v) for v in out)))
 
 
 CASES = [(1, 1, 1, 1), (96, 80, 4, 32), (500, 333, 13, 32), (1024, 1024, 16, 32), (1537, 1283, 33, 16),
@@ -57,7 +57,9 @@ def test_plan_covers_every_tile_once(lib, rows, cols, kb, batch):
     flat = (keys[:, 0] * mt + keys[:, 1]) * nt + keys[:, 2]
     assert len(flat) == len(np.unique(flat)) == mt * nt * batch
     pool = slots // 8 if p["shape"] == 0 and kb >= 128 and slots >= 256 else 0
-    assert slots - p["fixed"] == pool and p["grid"] == 8 * (slots + (-(-slots // 12) if pool else 0))
+    assert slots - p["fixed"] == pool
+    assert p["chain"] == int(p["shape"] == 0 and 5 <= kb <= 48 and slots > 32)
+    assert p["grid"] == (256 if p["chain"] else 8 * (slots + (-(-slots // 12) if pool else 0)))
     narrow = p["shape"] == 0 and min(mt, nt) == 1
     assert (p["deal"] == 2) == (mt * nt < (8 if narrow else 256 * PER_CU[p["shape"]]))
     if p["deal"] == 2:
@@ -75,3 +77,5 @@ def test_sizes_take_their_shapes(lib):
     for shape, sizes in SHAPES.items():
         for rows, cols, k, batch in sizes:
             assert plan(lib, rows, cols, -(-k // 64), batch)["shape"] == shape, (rows, cols, k, batch)
+    for rows, cols, k, batch in CHAINED:
+        assert plan(lib, rows, cols, -(-k // 64), batch)["chain"] == 1, (rows, cols, k, batch)

@@ -207,8 +207,8 @@ def test_gauss_maxima(o2m, m, n, k):
 
 # ------------------------------------------------------------------ GEMM tiles
 def _gemm_sizes():
-    from gemm_shapes import SHAPES
-    return [(s, *c) for s, cs in SHAPES.items() for c in cs]
+    from gemm_shapes import CHAINED, SHAPES
+    return [(s, *c) for s, cs in SHAPES.items() for c in cs] + [("chain", *c) for c in CHAINED]
 
 
 @pytest.mark.parametrize("shape,m,n,k,products", _gemm_sizes())
