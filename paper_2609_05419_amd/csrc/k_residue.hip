@@ -88,17 +88,24 @@ __device__ inline uint32_t pack4(uint32_t b0, uint32_t b1, uint32_t b2, uint32_t
     return __builtin_amdgcn_perm(hi, lo, 0x05040100u);                // [lo.0, lo.1, hi.0, hi.1]
 }
 
-// k entries per thread: one lane chunk of a fragment (16), or half of one for
-// four and five digits, whose int32 digits would otherwise hold the kernel to
-// one wave per SIMD; a fragment then goes to two waves, 32 chunks each.
-template <int D> constexpr int per_thread() { return D >= 4 ? 8 : 16; }
+// k entries per thread: one lane chunk of a fragment (16) for one digit, half
+// of one from two digits on, a fragment then going to two waves, 32 chunks
+// each.  With 16 entries the digits take 128 registers and more (two digits:
+// three waves per SIMD instead of four, three: two instead of four, four and
+// five: one), and the last round of waves costs more: residue phase at two
+// digits 2048^3 75 -> 68 us, 500 x 333 x 777 15.9 -> 13.3, 4096 x 96 x 4096
+// 159 -> 155, 8192^3 level; three digits 3000^3 N = 20 239 -> 221.  With one
+// digit (fp32 operands) 16 entries read whole lines with fewer loads: 8 took
+// 36 us instead of 30 for CGEMM 1537 x 1283 x 2051.
+template <int D> constexpr int per_thread() { return D == 1 ? 16 : 8; }
 
 // The split of the moduli (mchunk): waves that a launch is brought to, and
 // moduli that a wave keeps at least.  2048 waves are two per SIMD; below, the
-// serial chain of a wave is what takes the time (500 x 333 x 777, 896 waves:
-// residue phase 17.9 us whole, 15.7 in two parts, 18 in eight), above, the
-// entries read again cost more than the split gives (1024^3, 2048 waves: 24.8
-// us whole, 26.1 in two parts, 31.5 in four).
+// serial chain of a wave is what takes the time (500 x 333 x 777, 1456 waves:
+// residue phase 14.1 us whole, 13.0 in two parts, 13.9 in four, 16.3 in eight;
+// 96 x 80 x 200, 160 waves: 12.1 whole, 7.5 in eight), above, the entries read
+// again cost more than the split gives (700^3, 2112 waves: 14.8 whole, 15.7 in
+// two parts).
 constexpr long kResidueWaves = 2048;
 constexpr int kMinModuli = 2;
 
@@ -132,9 +139,9 @@ __device__ inline void store_words(int8_t *dst, const uint32_t (&w)[PT / 4]) {
 // D: base-2^26 digits of the quantized values (1..5, from their bound)
 // PAIRS (complex fp32, the host sets it when every pair is 16-byte aligned):
 // columns read two consecutive entries per 16-byte load; rows read rows 2i,
-// 2i + 1 of a column per 16-byte load, the even lane of a lane pair columns
-// kk0..kk0+7 and the odd lane kk0+8..kk0+15, and the pair then swaps halves so
-// that each lane holds its own row's 16 entries
+// 2i + 1 of a column per 16-byte load, the lane of the even row the first half
+// of its columns and the lane of the odd row the second, and the two then swap
+// so that each lane holds its own row's entries
 //
 // Workgroup row blockIdx.y computes the moduli [y mchunk, (y + 1) mchunk): a
 // wave's 2N residues per entry are a serial chain of ~100 instructions per
@@ -259,20 +266,21 @@ __global__ __launch_bounds__(256, D == 1 ? 3 : 1) void residue_kernel(ResidueArg
                 put(2 * e, (double)v[e].x, (double)v[e].y);
                 put(2 * e + 1, (double)v[e].z, (double)v[e].w);
             }
-        } else if constexpr (PT == 16) {   // (the host pairs rows up to three digits)
-            const bool odd = lane & 1;
-            const float2 *Xa = Xf + (r - (int)odd) + (size_t)(kk0 + (odd ? 8 : 0)) * ld;   // the pair's even row
-            float4 v[8];
+        } else {
+            constexpr int kPair = kHalves;          // lanes between a row and its pair's other row
+            const bool odd = lane & kPair;
+            const float2 *Xa = Xf + (r - (int)odd) + (size_t)(kk0 + (odd ? PT / 2 : 0)) * ld;   // the pair's even row
+            float4 v[PT / 2];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = *reinterpret_cast<const float4 *>(Xa + (size_t)j * ld);
+            for (int j = 0; j < PT / 2; ++j) v[j] = *reinterpret_cast<const float4 *>(Xa + (size_t)j * ld);
             settle();
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
+            for (int j = 0; j < PT / 2; ++j) {
                 // the even lane passes on its odd row's half, the odd lane its even row's
-                const float rx = __shfl_xor(odd ? v[j].x : v[j].z, 1, 64);
-                const float ry = __shfl_xor(odd ? v[j].y : v[j].w, 1, 64);
+                const float rx = __shfl_xor(odd ? v[j].x : v[j].z, kPair, 64);
+                const float ry = __shfl_xor(odd ? v[j].y : v[j].w, kPair, 64);
                 put(j, odd ? rx : v[j].x, odd ? ry : v[j].y);
-                put(8 + j, odd ? v[j].z : rx, odd ? v[j].w : ry);
+                put(PT / 2 + j, odd ? v[j].z : rx, odd ? v[j].w : ry);
             }
         }
     };
@@ -373,10 +381,9 @@ __global__ __launch_bounds__(256, D == 1 ? 3 : 1) void residue_kernel(ResidueArg
 
 static bool pairs_of(ElemType et, const ResidueSource &s) {
     // complex fp32 entries in 16-byte pairs when every pair is aligned: along
-    // a column (k-chunks start at even k) or across rows 2i, 2i + 1 (lane
-    // chunks of one row, up to three digits); an even ld and a 16-byte aligned
-    // base suffice
-    return et == kF32 && (s.mode == 1 || s.digits <= 3) && s.ld % 2 == 0 && ((uintptr_t)s.X & 15) == 0;
+    // a column (k-chunks start at even k) or across rows 2i, 2i + 1; an even
+    // ld and a 16-byte aligned base suffice
+    return et == kF32 && s.ld % 2 == 0 && ((uintptr_t)s.X & 15) == 0;
 }
 
 hipError_t launch_residues(ElemType et, bool split, int count, const ResidueSource *src, const ResidueParams &rp,
@@ -388,10 +395,10 @@ hipError_t launch_residues(ElemType et, bool split, int count, const ResidueSour
         const hipError_t e = launch_residues(et, split, 1, src, rp, st);
         return e != hipSuccess ? e : launch_residues(et, split, 1, src + 1, rp, st);
     }
-    // waves: one per fragment, two for four and five digits (per_thread)
+    // waves: one per fragment, two from two digits on (per_thread)
     long waves[2] = {0, 0};
     for (int i = 0; i < count; ++i)
-        waves[i] = (long)(src[i].g.rows_pad / kFragRows) * (long)src[i].g.kblocks * (digits >= 4 ? 2 : 1);
+        waves[i] = (long)(src[i].g.rows_pad / kFragRows) * (long)src[i].g.kblocks * (digits == 1 ? 1 : 2);
     const long blocks = (waves[0] + 3) / 4 + (waves[1] + 3) / 4;
     if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
     ResidueArgs a;
