@@ -416,18 +416,17 @@ __global__ __launch_bounds__(64 * kCombineWaves) void cs_combine_kernel(CsCombin
 }
 
 // ---- exponents straight from the operands --------------------------------
-// One launch finds the exponents of both sides: a workgroup of 16 waves takes
+// One launch finds the exponents of both sides: a workgroup of RB waves takes
 // RB operand rows with all their entries, so that nothing has to be combined
 // across workgroups and no buffer has to be cleared first.  Rows of a
-// column-major X: a workgroup takes 16 rows (64 measured 1.4-2x slower below
-// 2048 rows: too few workgroups), thread t row t % 16 of every 64th column;
-// columns of X: a wave per column.  Both rules: the maximum first, then
-// (Cauchy-Schwarz) the rule's sum against it, over the entries held in
-// registers (HOLD, up to kHold per thread) or read again.
+// column-major X: thread t takes row t % RB of every 64th column; columns of
+// X: a wave per column.  Both rules: the maximum first, then (Cauchy-Schwarz)
+// the rule's sum against it, over the entries held in registers (HOLD, up to
+// kHold per thread) or read again.
 // Bound at these sizes: launches and load latency.  Scale phase against the
-// chunked scans (3-4 launches): 96 x 80 x 200 14.4 -> 8.8 us, 500 x 333 x 777
-// 18.8 -> 11.6, 1024^3 18.1 -> 11.5 (max rule) and 22.5 -> 13.3, CGEMM
-// 1537 x 1283 x 2051 30.4 -> 18.9.
+// chunked scans (3-4 launches): 96 x 80 x 200 14.4 -> 6.8 us, 500 x 333 x 777
+// 18.8 -> 8.8, 1024^3 18.1 -> 10.4 (max rule) and 22.5 -> 12.2, CGEMM
+// 1537 x 1283 x 2051 30.4 -> 18.6.
 struct DirectSide {
     const void *X, *X2;          // X2: the second source of a rank-2k update, or null
     int ld, ld2, mode, count, k;
@@ -440,22 +439,20 @@ struct DirectArgs {
     int *status;
 };
 constexpr int kHold = 16;
-constexpr int kDirectK = 2560;                           // entries per operand row (direct_applies)
-constexpr size_t kDirectBytes = size_t(96) << 20;
+constexpr int kDirectK = 16384;                          // entries per operand row (direct_applies)
+constexpr size_t kDirectBytes = size_t(72) << 20;
 
-constexpr int kDirectRows = 16;   // operand rows per workgroup, either mode
-
-template <ElemType ET, bool CS, bool HOLD>
-__global__ __launch_bounds__(1024) void exponents_direct(DirectArgs a) {
+template <ElemType ET, bool CS, int RB, bool HOLD>
+__global__ __launch_bounds__(64 * RB) void exponents_direct(DirectArgs a) {
     const bool second = blockIdx.x >= a.blocks0;
     const DirectSide &o = a.s[second ? 1 : 0];
     const int block = (int)(blockIdx.x - (second ? a.blocks0 : 0u));
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     const bool cols = o.mode == 1;
-    constexpr int RB = kDirectRows;
     const int i = block * RB + (cols ? w : t % RB);
     const int ic = min(i, o.count - 1), k = o.k;
-    const int c0 = cols ? lane : t / RB, step = cols ? 64 : 1024 / RB;
+    const int c0 = cols ? lane : t / RB;
+    constexpr int step = 64;
     typedef typename Raw<ET>::T T;
     // entry c of the row (clamped; zero beyond k)
     auto entry = [&](const void *X, int ld, int c) {
@@ -488,7 +485,7 @@ __global__ __launch_bounds__(1024) void exponents_direct(DirectArgs a) {
             }
         }
     };
-    __shared__ unsigned long long sm[2][16][RB];
+    __shared__ unsigned long long sm[2][RB][RB];
     // op over the row's threads (both reductions use it, each its own sm)
     auto reduce = [&](unsigned long long v, int use, auto op) {
         if (cols) {
@@ -501,7 +498,7 @@ __global__ __launch_bounds__(1024) void exponents_direct(DirectArgs a) {
         __syncthreads();
         v = sm[use][0][t % RB];
 #pragma unroll
-        for (int q = 1; q < 16; ++q) v = op(v, sm[use][q][t % RB]);
+        for (int q = 1; q < RB; ++q) v = op(v, sm[use][q][t % RB]);
         return v;
     };
 
@@ -591,7 +588,7 @@ int row_chunk(int rows, int cols) {
     return chunk;
 }
 
-static size_t entry_bytes(ElemType et) { return et == kF64 ? 16 : 8; }
+constexpr size_t entry_bytes(ElemType et) { return et == kF64 ? 16 : 8; }
 
 // Non-temporal loads for operands of kStreamBytes and more.
 static bool streams(ElemType et, int rows, int cols) {
@@ -715,22 +712,43 @@ hipError_t launch_cs_combine(ElemType et, const CsCombineArgs &g, hipStream_t st
     return hipGetLastError();
 }
 
-// The direct kernel takes calls whose rows a workgroup reads in a few rounds
-// of loads (it walks a row alone: 300 x 300 x 4096 took 35.6 us against the
-// chunked scans' 34.1, 40 x 40 x 3000 was level, 1500 x 1500 x 2000 36.9
-// against 39.5) and whose operands the caches can hold for its second reading
-// (2048^3, 128 MiB: 52.7 against 45.7 us; 2048 x 2048 x 1024, 64 MiB: 22.9
-// against 31.2).
+// The direct kernel takes calls whose operands the caches can hold for its
+// second reading (2048 x 2048 x 1024, 64 MiB: 21.4 us against the chunked
+// scans' 31.2; 1500 x 1500 x 2000, 92 MiB: 39.8 against 39.5; 2048^3, 128 MiB:
+// 52.7 against 45.7), up to a row length where a workgroup's walk along its
+// rows alone evens out with the scans' parallel chunks (64 x 64 x 16000: 68.4
+// against 72.4; 300 x 300 x 4096: 23.2 against 33.6).
 bool direct_applies(ElemType et, const CsCombineArgs &g) {
     const size_t per_row = (size_t)g.k * (g.B2 ? 2 : 1);
     const size_t bytes = entry_bytes(et) * (per_row * (size_t)g.ca + (size_t)g.k * (size_t)g.cb);
     return per_row <= kDirectK && bytes <= kDirectBytes;
 }
 
+// Rows per workgroup: 16 once that gives kDirectGroups workgroups, half or a
+// quarter of it before, down to 4 (500 x 333 x 777: 11.6, 9.6, 8.8 us with 16,
+// 8, 4 rows; CGEMM 1537 x 1283 x 2051 18.6, 24.6, 33.9; 100 x 2000 x 2000 29.6
+// with 16, 35.1 with 8); complex fp64 held in registers 8, a whole 128-byte
+// line of a column (1024^3 12.0, 10.4, 12.3).
+constexpr int kDirectGroups = 120;
+
+template <ElemType ET, bool CS, int RB>
+static void launch_direct_rb(const DirectArgs &a, bool hold, unsigned blocks, hipStream_t st) {
+    if (!hold) exponents_direct<ET, CS, RB, false><<<blocks, 64 * RB, 0, st>>>(a);
+    else if constexpr (ET != kF64 || RB < 16) exponents_direct<ET, CS, RB, true><<<blocks, 64 * RB, 0, st>>>(a);
+}
+
 template <ElemType ET, bool CS>
-static void launch_direct_t(const DirectArgs &a, bool hold, unsigned blocks, hipStream_t st) {
-    if (hold) exponents_direct<ET, CS, true><<<blocks, 1024, 0, st>>>(a);
-    else exponents_direct<ET, CS, false><<<blocks, 1024, 0, st>>>(a);
+static void launch_direct_t(DirectArgs &a, hipStream_t st) {
+    const long ca = a.s[0].count, cb = a.s[1].count;
+    const bool hold = !a.s[0].X2 && a.s[0].k <= 64 * kHold;
+    int rb = hold && ET == kF64 ? 8 : 16;
+    while (rb > 4 && (ca + cb) / rb < kDirectGroups) rb >>= 1;
+    a.blocks0 = (unsigned)((ca + rb - 1) / rb);
+    const unsigned blocks = a.blocks0 + (unsigned)((cb + rb - 1) / rb);
+    if (blocks == 0) return;
+    if (rb == 4) launch_direct_rb<ET, CS, 4>(a, hold, blocks, st);
+    else if (rb == 8) launch_direct_rb<ET, CS, 8>(a, hold, blocks, st);
+    else launch_direct_rb<ET, CS, 16>(a, hold, blocks, st);
 }
 
 hipError_t launch_exponents_direct(ElemType et, bool cs, const CsCombineArgs &g, unsigned long long *amax_a,
@@ -740,19 +758,11 @@ hipError_t launch_exponents_direct(ElemType et, bool cs, const CsCombineArgs &g,
     a.s[0] = {g.A, g.B2, g.lda, g.ldb2, g.amode, g.ca, g.k, g.Ea, amax_a};
     a.s[1] = {g.B, nullptr, g.ldb, 0, g.bmode, g.cb, g.k, g.Eb, amax_b};
     a.status = g.status;
-    const bool hold = !g.B2 && g.k <= 64 * kHold;
-    a.blocks0 = (unsigned)(((long)g.ca + kDirectRows - 1) / kDirectRows);
-    const unsigned n = a.blocks0 + (unsigned)(((long)g.cb + kDirectRows - 1) / kDirectRows);
-    if (n == 0) return hipSuccess;
-    if (et == kI32) launch_direct_t<kI32, false>(a, hold, n, st);
-    else if (cs) {
-        if (et == kF64) launch_direct_t<kF64, true>(a, hold, n, st);
-        else if (et == kF32) launch_direct_t<kF32, true>(a, hold, n, st);
-        else launch_direct_t<kR64, true>(a, hold, n, st);
-    } else {
-        if (et == kF64) launch_direct_t<kF64, false>(a, hold, n, st);
-        else if (et == kF32) launch_direct_t<kF32, false>(a, hold, n, st);
-        else launch_direct_t<kR64, false>(a, hold, n, st);
+    switch (et) {
+    case kI32: launch_direct_t<kI32, false>(a, st); break;
+    case kF64: cs ? launch_direct_t<kF64, true>(a, st) : launch_direct_t<kF64, false>(a, st); break;
+    case kF32: cs ? launch_direct_t<kF32, true>(a, st) : launch_direct_t<kF32, false>(a, st); break;
+    case kR64: cs ? launch_direct_t<kR64, true>(a, st) : launch_direct_t<kR64, false>(a, st); break;
     }
     return hipGetLastError();
 }

@@ -132,12 +132,13 @@ def _special(x, rule):
     return x
 
 
-# The direct kernel takes 16 rows per workgroup, 64 entries of a row per round,
-# 16 rounds held in registers (k <= 1024), and calls up to 2560 entries per
-# row; past that the chunked scans run.
+# The direct kernel takes 4 rows per workgroup, 8 from 960 rows and 16 from 1920
+# (not complex fp64 with k <= 1024), 64 entries of a row per round, 16 rounds
+# held in registers (k <= 1024), and calls up to 16384 entries per row; past
+# that the chunked scans run.
 @pytest.mark.parametrize("rule", ["max", "cs"])
 @pytest.mark.parametrize("m,n,k", [(1, 1, 1), (15, 17, 63), (16, 16, 64), (17, 15, 65), (33, 31, 1024), (18, 20, 1025),
-                                   (6, 7, 2560), (7, 6, 2561), (2, 2, 0)])
+                                   (700, 263, 20), (959, 964, 9), (1915, 18, 1026), (6, 7, 16384), (7, 6, 16385), (2, 2, 0)])
 def test_exponents(o2m, m, n, k, rule):
     a = _special(W.complex_matrix(m, k, 41, dist="phi", phi=2.0), rule) if k else np.zeros((m, 0), np.complex128)
     b = _special(W.complex_matrix(n, k, 42, dist="phi", phi=2.0), rule).T if k else np.zeros((0, n), np.complex128)
@@ -159,9 +160,9 @@ def test_exponents(o2m, m, n, k, rule):
 
 
 @pytest.mark.parametrize("rule", ["max", "cs"])
-@pytest.mark.parametrize("n,k", [(17, 65), (33, 1280), (18, 1281), (20, 2561)])
+@pytest.mark.parametrize("n,k", [(17, 65), (965, 9), (33, 1030), (18, 8192), (18, 8193), (20, 16385)])
 def test_exponents_symmetric(o2m, n, k, rule):
-    """Both sources of a rank-2k update count towards the limit (1280 each)."""
+    """Both sources of a rank-2k update count towards the limit (8192 each)."""
     a, b = (_special(W.complex_matrix(n, k, s, dist="phi", phi=1.0), rule) for s in (51, 52))
     b[4:6, :] = 0                                        # the straddling rows of [A | B] are A's
     ra, rb = a.real.copy(order="F"), b.real.copy(order="F")
@@ -173,7 +174,7 @@ def test_exponents_symmetric(o2m, n, k, rule):
         assert same_bits(host(got)[tri], np.asarray(ref)[tri])
 
 
-@pytest.mark.parametrize("k", [40, 1030, 2570])
+@pytest.mark.parametrize("k", [40, 1030, 16390])
 @pytest.mark.parametrize("rule", ["max", "cs"])
 def test_exponents_nonfinite(o2m, k, rule):
     """Inf or NaN in a row or column: NaN there, the status bit, the rest exact."""
@@ -193,7 +194,7 @@ def test_exponents_nonfinite(o2m, k, rule):
     assert same_bits(got[~bad], clean[~bad])
 
 
-@pytest.mark.parametrize("m,n,k", [(17, 15, 65), (3, 5, 2560), (5, 3, 2561)])
+@pytest.mark.parametrize("m,n,k", [(17, 15, 65), (3, 5, 16384), (5, 3, 16385)])
 def test_gauss_maxima(o2m, m, n, k):
     """The bound check reads the maxima of whichever kernel found them."""
     A, B = W.gauss_matrix(m, k, 7, lo=-50, hi=50), W.gauss_matrix(k, n, 8, lo=-50, hi=50)
