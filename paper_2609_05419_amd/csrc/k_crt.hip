@@ -57,23 +57,23 @@ __device__ inline typename OutT<OT>::type finish(const double (&sre)[T], const d
 
 // MODE 0: ZGEMM / CGEMM output.  MODE 3: exact Gaussian integers (int64).
 // MODE 4: residue hook (per-modulus 2M post output).  Each thread owns R = 4
-// consecutive rows of one column: one dword per plane.  Up to three limbs
+// consecutive rows of one column, one dword per plane, or one row (launch_rows).  Up to three limbs
 // the row exponents are fetched before the limb sums and the kernel is held
 // to 80 registers (six waves per SIMD; it needs 81 otherwise); with more
 // limbs both would cost occupancy or spills, and the exponents are read when
 // the rows are finished.
-template <int T, int MODE, ElemType OT>
+template <int T, int MODE, ElemType OT, int R>
 __global__ __launch_bounds__(256, T <= 3 ? 6 : 1) void crt_kernel(CrtArgs a, CrtParams cp) {
-    constexpr int R = 4;
+    typedef typename std::conditional<R == 4, uint32_t, uint8_t>::type Word;   // R residues of a plane
     const int rows_per_block = 256 * R;
     const int mblocks = (a.m + rows_per_block - 1) / rows_per_block;
     const int j = blockIdx.x / mblocks;
     const int i0 = ((blockIdx.x % mblocks) * 256 + threadIdx.x) * R;
-    // complex outputs pass through LDS in their stored type (each wave its own
-    // 256 entries) and leave in row order, so a lane may store rows of another
+    // with four rows per thread complex outputs pass through LDS in their stored
+    // type (each wave its own 256 entries) and leave in row order, so a lane may store rows of another
     // lane: a wave leaves only when all its rows are beyond m, and a lane
     // beyond m reads row 0 instead (its sums are never stored)
-    constexpr bool STAGE = MODE == 0;
+    constexpr bool STAGE = MODE == 0 && R > 1;
     typedef typename OutT<OT>::type SV;
     __shared__ SV stage[STAGE ? 256 * R : 1];
     const int lane = threadIdx.x & 63, w0 = threadIdx.x & ~63;
@@ -115,8 +115,12 @@ __global__ __launch_bounds__(256, T <= 3 ? 6 : 1) void crt_kernel(CrtArgs a, Crt
     constexpr bool EARLY = MODE == 0 && T <= 3;
     int ev[R] = {}, fj = 0;
     if constexpr (EARLY) {
-        const int4 e4 = *reinterpret_cast<const int4 *>(a.E + (i0 < a.m ? i0 : 0));
-        ev[0] = e4.x; ev[1] = e4.y; ev[2] = e4.z; ev[3] = e4.w;
+        if constexpr (R == 4) {
+            const int4 e4 = *reinterpret_cast<const int4 *>(a.E + (i0 < a.m ? i0 : 0));
+            ev[0] = e4.x; ev[1] = e4.y; ev[2] = e4.z; ev[3] = e4.w;
+        } else {
+            ev[0] = a.E[i0];
+        }
         fj = a.F[j];
     }
 
@@ -133,8 +137,8 @@ __global__ __launch_bounds__(256, T <= 3 ? 6 : 1) void crt_kernel(CrtArgs a, Crt
         uint32_t wp[CH], wm[CH];
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
-            wp[c] = *reinterpret_cast<const uint32_t *>(base + (size_t)(2 * (l0 + c)) * a.plane_bytes);
-            wm[c] = *reinterpret_cast<const uint32_t *>(base + (size_t)(2 * (l0 + c) + 1) * a.plane_bytes);
+            wp[c] = *reinterpret_cast<const Word *>(base + (size_t)(2 * (l0 + c)) * a.plane_bytes);
+            wm[c] = *reinterpret_cast<const Word *>(base + (size_t)(2 * (l0 + c) + 1) * a.plane_bytes);
         }
 #pragma unroll
         for (int c = 0; c < CH; ++c)
@@ -165,7 +169,7 @@ __global__ __launch_bounds__(256, T <= 3 ? 6 : 1) void crt_kernel(CrtArgs a, Crt
         for (int c = 0; c < CH; ++c) {
             const size_t p0 = (size_t)(2 * cp.n2 + 3 * (l0 + c - cp.n2));
 #pragma unroll
-            for (int q = 0; q < 3; ++q) w[c][q] = *reinterpret_cast<const uint32_t *>(base + (p0 + q) * a.plane_bytes);
+            for (int q = 0; q < 3; ++q) w[c][q] = *reinterpret_cast<const Word *>(base + (p0 + q) * a.plane_bytes);
         }
 #pragma unroll
         for (int c = 0; c < CH; ++c)
@@ -256,12 +260,12 @@ __global__ __launch_bounds__(256, REAL_ONLY ? 1 : (T <= 3 ? 6 : 5)) void crt_sym
     // store writes whole 128-byte lines across 8 lanes
     const int jl = tid >> 3, r0 = tid & 7;
 
-    // a fresh output: zeros to the mirrored tile's strict other triangle, in
-    // the same layout, while the first copies are on their way
+    // a fresh output: zeros to the mirrored tile's strict other triangle, whole
+    // columns of it per half wave
     if (a.zero_other) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const int i = J * 32 + r0 + 8 * e, j = I * 32 + jl;
+            const int i = J * 32 + (tid & 31), j = I * 32 + (tid >> 5) + 8 * e;
             if (i >= a.n || j >= a.n || (a.upper ? i <= j : i >= j)) continue;
             if (REAL_ONLY) reinterpret_cast<double *>(a.c)[(size_t)i + (size_t)j * a.ldc] = 0.0;
             else reinterpret_cast<double2 *>(a.c)[(size_t)i + (size_t)j * a.ldc] = make_double2(0.0, 0.0);
@@ -352,6 +356,24 @@ __global__ __launch_bounds__(256, REAL_ONLY ? 1 : (T <= 3 ? 6 : 5)) void crt_sym
     }
 }
 
+// One row per thread for outputs up to 2^20 entries, where a thread's serial
+// chain over four rows takes the time rather than the traffic (CRT phase: 96 x
+// 80 10.2 -> 7.6 us, 500 x 333 10.7 -> 8.3, 500 x 500 N = 28 18.9 -> 12.8, 1300
+// x 700 18.9 -> 17.2; level at 1000 x 1000, 1000 x 4000 40.0 -> 42.7), and for
+// columns of up to 160 rows, which fill 40 lanes of a wave with four rows per
+// thread (64 x 50000 137 -> 64 us, 150 x 30000 97 -> 83; 300 x 20000 97 -> 121).
+constexpr long kSmallOutput = 1L << 20;
+constexpr int kShortColumn = 160;
+
+template <int T, int MODE, ElemType OT>
+void launch_rows(const CrtArgs &ca, const CrtParams &cp, hipStream_t st) {
+    const bool single = ca.m <= kShortColumn || (long)ca.m * ca.n <= kSmallOutput;
+    const int per = single ? 256 : 1024;      // rows per workgroup
+    const unsigned blocks = (unsigned)(((long)ca.m + per - 1) / per * ca.n);
+    if (single) crt_kernel<T, MODE, OT, 1><<<blocks, 256, 0, st>>>(ca, cp);
+    else crt_kernel<T, MODE, OT, 4><<<blocks, 256, 0, st>>>(ca, cp);
+}
+
 template <int T>
 hipError_t launch_t(int mode, ElemType ot, const CrtArgs &ca, const CrtParams &cp, hipStream_t st) {
     if (mode == 1 || mode == 2) {
@@ -370,10 +392,10 @@ hipError_t launch_t(int mode, ElemType ot, const CrtArgs &ca, const CrtParams &c
     // 4 rows of one column per thread, 1024 rows per workgroup
     const long blocks = (long)((ca.m + 1023) / 1024) * ca.n;
     if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
-    if (mode == 0 && ot == kF64) crt_kernel<T, 0, kF64><<<(unsigned)blocks, 256, 0, st>>>(ca, cp);
-    else if (mode == 0 && ot == kF32) crt_kernel<T, 0, kF32><<<(unsigned)blocks, 256, 0, st>>>(ca, cp);
-    else if (mode == 3 && T == 2) crt_kernel<2, 3, kF64><<<(unsigned)blocks, 256, 0, st>>>(ca, cp);
-    else if (mode == 4) crt_kernel<T, 4, kF64><<<(unsigned)blocks, 256, 0, st>>>(ca, cp);
+    if (mode == 0 && ot == kF64) launch_rows<T, 0, kF64>(ca, cp, st);
+    else if (mode == 0 && ot == kF32) launch_rows<T, 0, kF32>(ca, cp, st);
+    else if (mode == 3 && T == 2) launch_rows<2, 3, kF64>(ca, cp, st);
+    else if (mode == 4) crt_kernel<T, 4, kF64, 4><<<(unsigned)blocks, 256, 0, st>>>(ca, cp);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }

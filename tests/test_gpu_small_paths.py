@@ -237,3 +237,33 @@ def test_gemm_tiles_symmetric(o2m, n, k):
     ent = [(i, j) for i in (0, n - 1) for j in (0, n - 1) if i >= j]
     ent += [(max(i, j), min(i, j)) for i, j in rng.integers(0, n, (400, 2)).tolist()]
     assert same_bits(np.array([got[i, j] for i, j in ent]), O.oq_zherk(a, 16, entries=ent))
+
+
+# ------------------------------------------------------------------ CRT
+# One row per thread up to 160 rows or 2^20 entries, four beyond: both sides of
+# either line, wave and workgroup edges, two to six limbs.
+@pytest.mark.parametrize("m,n,N", [(1, 300, 16), (63, 70, 8), (65, 64, 20), (160, 40, 26), (161, 41, 31), (255, 9, 16),
+                                   (257, 9, 18), (1025, 5, 8), (1024, 1024, 8), (1025, 1024, 16), (1030, 1027, 20),
+                                   (161, 6600, 26), (1281, 1000, 31), (160, 6600, 16)])
+def test_crt_rows(o2m, m, n, N):
+    k = 3
+    a, b = W.complex_matrix(m, k, 21, dist="phi", phi=1.0), W.complex_matrix(k, n, 22, dist="phi", phi=1.0)
+    cols = sorted({0, n // 3, n - 2 if n > 1 else 0, n - 1})
+    ent = [(i, j) for j in cols for i in range(m)]
+    for dt, fn, ref in ((np.complex128, o2m.zgemm_2m, O.oq_zgemm), (np.complex64, o2m.cgemm_2m, O.oq_cgemm)):
+        x, y = a.astype(dt), b.astype(dt)
+        out = torch.full((n, m + 3), complex("nan"), dtype=torch.from_numpy(x).dtype, device=DEV)
+        got = fn(to_dev(x), to_dev(y), n_moduli=N, out=out[:, :m].t())
+        assert torch.isnan(out[:, m:].real).all()                # nothing beyond the rows is written
+        assert not torch.isnan(out[:, :m].real).any()            # and every row is
+        got = host(got)
+        assert same_bits(np.array([got[i, j] for i, j in ent]), ref(x, y, N, entries=ent))
+
+
+@pytest.mark.parametrize("m,n", [(3, 5), (161, 7), (257, 3), (1030, 1030)])
+def test_crt_rows_gauss(o2m, m, n):
+    A, B = W.gauss_matrix(m, 4, 23), W.gauss_matrix(4, n, 24)
+    dA, dB = (torch.from_numpy(x).to(DEV).transpose(0, 1) for x in (A, B))
+    o2m.get_status()
+    got = o2m.gauss_gemm_2m(dA, dB, n_moduli=4).transpose(0, 1).cpu().numpy()
+    assert o2m.get_status() == 0 and np.array_equal(got, O.gauss_4m(A, B))
