@@ -392,9 +392,10 @@ o2m_status run(const Call &c) {
         // settle (the few entries they leave open are summed from the data)
         b.csa.chunks = cs_chunks(amode, a_rows, a_cols) * g.halves;
         b.csb.chunks = sym ? 0 : cs_chunks(bmode, b_rows, b_cols);
-        O2M_TRY(launch_cs_scan(amode, et, a_rows, a_cols, c.A, c.lda, b.csa, 0, c.st));
-        if (two) O2M_TRY(launch_cs_scan(0, et, c.m, c.k, c.B, c.ldb, b.csa, b.csa.chunks / 2, c.st));
-        if (!sym) O2M_TRY(launch_cs_scan(bmode, et, b_rows, b_cols, c.B, c.ldb, b.csb, 0, c.st));
+        CsScan scan[2] = {{c.A, a_rows, a_cols, c.lda, amode, b.csa, 0}, {}};
+        if (two) scan[1] = {c.B, c.m, c.k, c.ldb, 0, b.csa, b.csa.chunks / 2};
+        else if (!sym) scan[1] = {c.B, b_rows, b_cols, c.ldb, bmode, b.csb, 0};
+        O2M_TRY(launch_cs_scan(et, two || !sym ? 2 : 1, scan, c.st));
         cg.pa = b.csa;
         cg.pb = b.csb;
         O2M_TRY(launch_cs_combine(et, cg, c.st));

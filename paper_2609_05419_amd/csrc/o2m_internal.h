@@ -144,8 +144,14 @@ struct CsPartials {
 };
 // Chunks per entry that one source of rows x cols gives in `mode`.
 int cs_chunks(int mode, int rows, int cols);
-hipError_t launch_cs_scan(int mode, ElemType et, int rows, int cols, const void *X, int ld, const CsPartials &p,
-                          int chunk_ofs, hipStream_t st);
+struct CsScan {
+    const void *X;
+    int rows, cols, ld, mode;
+    CsPartials p;
+    int chunk_ofs;
+};
+// One or two operands, in one launch where their shapes allow it.
+hipError_t launch_cs_scan(ElemType et, int count, const CsScan *src, hipStream_t st);
 // Pass 2: E and the Cauchy-Schwarz exponent of every row of A (ca) and column
 // of B (cb) from the records (INT32_MIN and kStatusNonfinite for Inf/NaN, 0
 // for zero rows); an entry whose records leave the exponent open is summed

@@ -267,3 +267,21 @@ def test_crt_rows_gauss(o2m, m, n):
     o2m.get_status()
     got = o2m.gauss_gemm_2m(dA, dB, n_moduli=4).transpose(0, 1).cpu().numpy()
     assert o2m.get_status() == 0 and np.array_equal(got, O.gauss_4m(A, B))
+
+
+# ------------------------------------------------------------------ chunked scans
+# Past the direct kernel's rows (16384): two operands in one launch (row scan
+# beside column scan, two row scans, two column scans, rank-2k), and apart
+# (column pairs of one fp32 operand only).
+@pytest.mark.parametrize("call,m,n,k,ta,tb,pad", [("z", 7, 9, 16390, "N", "N", (0, 0)), ("z", 9, 7, 16385, "N", "T", (1, 1)),
+                                                  ("z", 6, 65, 16401, "T", "N", (0, 2)), ("z", 65, 6, 16400, "C", "T", (1, 0)),
+                                                  ("c", 8, 6, 16386, "N", "N", (0, 0)), ("c", 7, 9, 16387, "T", "N", (1, 1)),
+                                                  ("c", 6, 8, 16388, "T", "N", (0, 1)), ("c", 5, 9, 16385, "N", "T", (1, 1))])
+def test_scans_of_two_operands(o2m, call, m, n, k, ta, tb, pad):
+    dt = np.complex64 if call == "c" else np.complex128
+    a = _special(W.complex_matrix(m, k, 11, dist="phi", phi=1.0).astype(dt), "cs")
+    b = np.asfortranarray(_special(W.complex_matrix(n, k, 12, dist="phi", phi=1.0).astype(dt), "cs").T)
+    A, B = np.asfortranarray(op_of(a, ta)), np.asfortranarray(op_of(b, tb))   # op is its own inverse
+    fn, ref = (o2m.cgemm_2m_op, O.oq_cgemm) if call == "c" else (o2m.zgemm_2m_op, O.oq_zgemm)
+    got = host(fn(padded(A, pad[0]), padded(B, pad[1]), ta, tb, n_moduli=16, scaling="cs"))
+    assert same_bits(got, ref(a, b, 16, scaling="cs"))
