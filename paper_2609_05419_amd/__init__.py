@@ -110,12 +110,17 @@ def _ld(x: torch.Tensor) -> int:
 
 
 def _stream(stream) -> int:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    if stream is None:
+        # torch.cuda.current_stream().cuda_stream without the Stream object
+        return _raw_stream(torch.cuda.current_device()) if _raw_stream else torch.cuda.current_stream().cuda_stream
+    return stream.cuda_stream
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _empty_colmajor(rows: int, cols: int, dtype, device) -> torch.Tensor:
-    return torch.empty((cols, rows), dtype=dtype, device=device).t()
+    return torch.empty_strided((rows, cols), (1, max(rows, 1)), dtype=dtype, device=device)
 
 
 def _check_operands(A, B, dtype):
