@@ -137,7 +137,12 @@ O2M_HD inline GemmSchedule gemm_schedule(int mt, int nt, int kblocks, int batch,
 // with the CU full, `latency` what a stage costs however empty the CU is.  The
 // constants fit the GEMM phase of 30 shapes from 60^3 to 4096^3 measured with
 // each of the four (to 8-11%); the estimate's choice is the fastest or within
-// 7% of it on all of them.  Large products take the 256 x 256 tile, which
+// 7% of it on all of them.  A launch long enough to be held by its power draw
+// pays for the extra data that the smaller tiles move: their stages cost up to
+// 16% more (`sustained`, by the large tile's estimate in units of 600 us; 3492
+// x 1543 x 16566 at N = 14: 2033 us with the large tile, 2312 with 256 x 128,
+// estimated 2021 and 2017 without this; 1100 x 1100 x 8192: 342 and 310).
+// Large products take the 256 x 256 tile, which
 // moves the least data per MFMA (2048^3: 230 us against 241, 271 and 447);
 // short k, ragged sizes and products of fewer tiles than CUs the smaller ones
 // (700^3: 34.0, 27.7, 25.2, 28.5; 96 x 80 x 200: 13.0, 10.6, 8.6, 7.2;
@@ -158,10 +163,12 @@ O2M_HD inline GemmShape gemm_shape_of(int i) {
     return shapes[i];
 }
 
-O2M_HD inline double gemm_estimate(const GemmShape &s, long rows, long cols, int kblocks, int batch) {
+O2M_HD inline double gemm_estimate(const GemmShape &s, long rows, long cols, int kblocks, int batch,
+                                   double sustained = 0.0) {
     const long tiles = (rows + s.tm - 1) / s.tm * ((cols + s.tn - 1) / s.tn) * batch;
     const double rounds = (double)((tiles + kCus - 1) / kCus) / s.per_cu;
-    return s.launch + rounds * (s.tile + s.stage * kblocks) + s.latency * kblocks;
+    const double stage = s.stage * (1.0 + 0.16 * (sustained < 1.0 ? sustained : 1.0));
+    return s.launch + rounds * (s.tile + stage * kblocks) + s.latency * kblocks;
 }
 
 // The launch of one batched int8 GEMM: tile shape, tiles and schedule.
@@ -192,10 +199,11 @@ constexpr int kChainMin = 5, kChainMax = 48;
 O2M_HD inline GemmPlan gemm_plan(int rows, int cols, int kblocks, int batch, long stage_bytes) {
     GemmPlan p = {0, 0, 0, 0, 0, 0, {0, 0, 0, 0, 0}};
     if (rows <= 0 || cols <= 0 || batch <= 0 || kblocks <= 0) return p;
-    double best = 0.0;
-    for (int i = 0; i < kGemmShapes; ++i) {
-        const double t = gemm_estimate(gemm_shape_of(i), rows, cols, kblocks, batch);
-        if (i == 0 || t < best) {
+    const double large = gemm_estimate(gemm_shape_of(0), rows, cols, kblocks, batch);
+    double best = large;
+    for (int i = 1; i < kGemmShapes; ++i) {
+        const double t = gemm_estimate(gemm_shape_of(i), rows, cols, kblocks, batch, large / 600.0);
+        if (t < best) {
             best = t;
             p.shape = i;
         }

@@ -9,8 +9,8 @@ void t_plan(int rows, int cols, int kblocks, int batch, long stage_bytes, long *
     const long v[11] = {p.shape, p.tm, p.tn, p.mt, p.nt, p.s.deal, p.s.chunk, p.s.slots, p.s.fixed, p.s.grid, p.chain};
     for (int i = 0; i < 11; ++i) out[i] = v[i];
 }
-double t_estimate(int shape, int rows, int cols, int kblocks, int batch) {
-    return o2m::gemm_estimate(o2m::gemm_shape_of(shape), rows, cols, kblocks, batch);
+double t_estimate(int shape, int rows, int cols, int kblocks, int batch, double sustained) {
+    return o2m::gemm_estimate(o2m::gemm_shape_of(shape), rows, cols, kblocks, batch, sustained);
 }
 // tiles[4 * (x * slots + slot) + {valid, p, ti, tj}]
 void t_plan_tiles(int mt, int nt, int chunk, int deal, int batch, long slots, int *tiles) {

@@ -24,7 +24,7 @@ def lib(tmp_path_factory):
     L = ctypes.CDLL(str(out))
     I, Lg, P = ctypes.c_int, ctypes.c_long, ctypes.c_void_p
     L.t_plan.argtypes = [I, I, I, I, Lg, P]
-    L.t_estimate.argtypes = [I, I, I, I, I]
+    L.t_estimate.argtypes = [I, I, I, I, I, ctypes.c_double]
     L.t_estimate.restype = ctypes.c_double
     L.t_plan_tiles.argtypes = [I, I, I, I, I, Lg, P]
     return L
@@ -48,7 +48,8 @@ def test_plan_covers_every_tile_once(lib, rows, cols, kb, batch):
     p = plan(lib, rows, cols, kb, batch)
     mt, nt, slots = p["mt"], p["nt"], p["slots"]
     assert (mt - 1) * p["tm"] < rows <= mt * p["tm"] and (nt - 1) * p["tn"] < cols <= nt * p["tn"]
-    est = [lib.t_estimate(i, rows, cols, kb, batch) for i in range(4)]
+    est = [lib.t_estimate(0, rows, cols, kb, batch, 0.0)]
+    est += [lib.t_estimate(i, rows, cols, kb, batch, est[0] / 600) for i in (1, 2, 3)]
     assert est[p["shape"]] == min(est)
     t = np.zeros((8, slots, 4), dtype=np.int32)
     lib.t_plan_tiles(mt, nt, p["chunk"], p["deal"], batch, slots, t.ctypes.data)
