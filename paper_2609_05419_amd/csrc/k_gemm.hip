@@ -30,7 +30,9 @@
 // Which workgroup computes which tile is set out in tile_schedule.h: fixed
 // slots by workgroup index, and on long launches a pool of slots per XCD
 // that workgroups claim at run time (claim_slot below), so that XCDs running
-// at different clocks finish together.
+// at different clocks finish together.  Products of short k chain several of
+// these tiles per workgroup (gemm_i8_chain), and small, ragged or narrow ones
+// take smaller tiles (gemm_i8_multi): gemm_plan chooses.
 
 // Bound: int8 MFMA.  Algorithmic work per launch = 2 m n k int8 ops per
 // product (counting the padded-free m, n, k of the problem).
