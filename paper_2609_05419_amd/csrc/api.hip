@@ -382,7 +382,7 @@ o2m_status run(const Call &c) {
     cg.amode = amode;
     cg.bmode = bmode;
     const bool gauss = c.op == kOpG;
-    if (direct_applies(et, cg)) {
+    if (direct_applies(et, cs && !gauss, cg)) {
         if (gm.fixed < gm.slots) O2M_TRY(launch_zero(b.queue, kQueueBytes, c.st));
         O2M_TRY(launch_exponents_direct(et, cs && !gauss, cg, gauss ? b.amax_a : nullptr, gauss ? b.amax_b : nullptr,
                                         c.st));

@@ -26,6 +26,7 @@
 // owns a chunk of one column.
 #include "o2m_internal.h"
 #include "cs_bounds.h"
+#include "scale_rules.h"
 
 #include <string.h>
 
@@ -465,12 +466,15 @@ __global__ __launch_bounds__(64 * kCombineWaves) void cs_combine_kernel(CsCombin
 // across workgroups and no buffer has to be cleared first.  Rows of a
 // column-major X: thread t takes row t % RB of every 64th column; columns of
 // X: a wave per column.  Both rules: the maximum first, then (Cauchy-Schwarz)
-// the rule's sum against it, over the entries held in registers (HOLD, up to
-// kHold per thread) or read again.
+// the rule's sum against it, over the HOLD entries a thread holds in registers
+// or, where HOLD is 0, read again (direct_hold, scale_rules.h).
 // Bound at these sizes: launches and load latency.  Scale phase against the
 // chunked scans (3-4 launches): 96 x 80 x 200 14.4 -> 6.8 us, 500 x 333 x 777
 // 18.8 -> 8.8, 1024^3 18.1 -> 10.4 (max rule) and 22.5 -> 12.2, CGEMM
-// 1537 x 1283 x 2051 30.4 -> 18.6.
+// 1537 x 1283 x 2051 30.4 -> 18.6.  With 16 held entries for every row of up to
+// 1024 a thread loaded and summed all 16 whatever k: 16384 x 1 x 64 took 26.7 us
+// under the Cauchy-Schwarz rule, 10.9 with one, 16384 x 1 x 200 27.0 and 14.7
+// with four, CGEMM 16384 x 1 x 512 34.8 and 20.5 with eight.
 struct DirectSide {
     const void *X, *X2;          // X2: the second source of a rank-2k update, or null
     int ld, ld2, mode, count, k;
@@ -482,11 +486,8 @@ struct DirectArgs {
     unsigned blocks0;            // workgroups of s[0]
     int *status;
 };
-constexpr int kHold = 16;
-constexpr int kDirectK = 16384;                          // entries per operand row (direct_applies)
-constexpr size_t kDirectBytes = size_t(72) << 20;
 
-template <ElemType ET, bool CS, int RB, bool HOLD>
+template <ElemType ET, bool CS, int RB, int HOLD>
 __global__ __launch_bounds__(64 * RB) void exponents_direct(DirectArgs a) {
     const bool second = blockIdx.x >= a.blocks0;
     const DirectSide &o = a.s[second ? 1 : 0];
@@ -511,11 +512,11 @@ __global__ __launch_bounds__(64 * RB) void exponents_direct(DirectArgs a) {
             if (c + u * step >= k) v[u] = Raw<ET>::zero();
     };
     // f over all entries of this thread
-    T held[HOLD ? kHold : 1];
+    T held[HOLD > 0 ? HOLD : 1];
     auto each = [&](auto f) {
-        if constexpr (HOLD) {
+        if constexpr (HOLD > 0) {
 #pragma unroll
-            for (int u = 0; u < kHold; ++u) f(held[u]);
+            for (int u = 0; u < HOLD; ++u) f(held[u]);
         } else {
             for (int src = 0; src < 2; ++src) {
                 const void *X = src ? o.X2 : o.X;
@@ -548,7 +549,7 @@ __global__ __launch_bounds__(64 * RB) void exponents_direct(DirectArgs a) {
 
     unsigned long long best = 0;
     if (k > 0) {
-        if constexpr (HOLD) batch(o.X, o.ld, c0, held, kHold);
+        if constexpr (HOLD > 0) batch(o.X, o.ld, c0, held, HOLD);
         each([&](T v) { best = umax(best, Raw<ET>::bits(v)); });
     }
     best = reduce(best, 0, [](unsigned long long x, unsigned long long y) { return umax(x, y); });
@@ -792,16 +793,9 @@ hipError_t launch_cs_combine(ElemType et, const CsCombineArgs &g, hipStream_t st
     return hipGetLastError();
 }
 
-// The direct kernel takes calls whose operands the caches can hold for its
-// second reading (2048 x 2048 x 1024, 64 MiB: 21.4 us against the chunked
-// scans' 31.2; 1500 x 1500 x 2000, 92 MiB: 39.8 against 39.5; 2048^3, 128 MiB:
-// 52.7 against 45.7), up to a row length where a workgroup's walk along its
-// rows alone evens out with the scans' parallel chunks (64 x 64 x 16000: 68.4
-// against 72.4; 300 x 300 x 4096: 23.2 against 33.6).
-bool direct_applies(ElemType et, const CsCombineArgs &g) {
-    const size_t per_row = (size_t)g.k * (g.B2 ? 2 : 1);
-    const size_t bytes = entry_bytes(et) * (per_row * (size_t)g.ca + (size_t)g.k * (size_t)g.cb);
-    return per_row <= kDirectK && bytes <= kDirectBytes;
+bool direct_applies(ElemType et, bool cs, const CsCombineArgs &g) {
+    const long rows = (g.amode == 0 ? g.ca : 0L) + (g.bmode == 0 ? g.cb : 0L);
+    return direct_rule(entry_bytes(et), cs, g.k, g.B2 != nullptr, rows, (long)g.ca + g.cb - rows);
 }
 
 // Rows per workgroup: 16 once that gives kDirectGroups workgroups, half or a
@@ -812,16 +806,24 @@ bool direct_applies(ElemType et, const CsCombineArgs &g) {
 constexpr int kDirectGroups = 120;
 
 template <ElemType ET, bool CS, int RB>
-static void launch_direct_rb(const DirectArgs &a, bool hold, unsigned blocks, hipStream_t st) {
-    if (!hold) exponents_direct<ET, CS, RB, false><<<blocks, 64 * RB, 0, st>>>(a);
-    else if constexpr (ET != kF64 || RB < 16) exponents_direct<ET, CS, RB, true><<<blocks, 64 * RB, 0, st>>>(a);
+static void launch_direct_rb(const DirectArgs &a, int hold, unsigned blocks, hipStream_t st) {
+    if (hold == 0) exponents_direct<ET, CS, RB, 0><<<blocks, 64 * RB, 0, st>>>(a);
+    else if constexpr (ET != kF64 || RB < 16) {
+        static_assert(kHold == 16, "the held forms of direct_hold");
+        switch (hold) {
+        case 1: exponents_direct<ET, CS, RB, 1><<<blocks, 64 * RB, 0, st>>>(a); break;
+        case 4: exponents_direct<ET, CS, RB, 4><<<blocks, 64 * RB, 0, st>>>(a); break;
+        case 8: exponents_direct<ET, CS, RB, 8><<<blocks, 64 * RB, 0, st>>>(a); break;
+        default: exponents_direct<ET, CS, RB, 16><<<blocks, 64 * RB, 0, st>>>(a); break;
+        }
+    }
 }
 
 template <ElemType ET, bool CS>
 static void launch_direct_t(DirectArgs &a, hipStream_t st) {
     const long ca = a.s[0].count, cb = a.s[1].count;
-    const bool hold = !a.s[0].X2 && a.s[0].k <= 64 * kHold;
-    int rb = hold && ET == kF64 ? 8 : 16;
+    const int hold = direct_hold(a.s[0].k, a.s[0].X2 != nullptr);
+    int rb = hold > 0 && ET == kF64 ? 8 : 16;
     while (rb > 4 && (ca + cb) / rb < kDirectGroups) rb >>= 1;
     a.blocks0 = (unsigned)((ca + rb - 1) / rb);
     const unsigned blocks = a.blocks0 + (unsigned)((cb + rb - 1) / rb);

@@ -171,8 +171,8 @@ struct CsCombineArgs {
 hipError_t launch_cs_combine(ElemType et, const CsCombineArgs &g, hipStream_t st);
 // Either rule's exponents of both sides in one launch, straight from the
 // operands (of g: all but the chunk records); gauss: the maxima into amax_a,
-// amax_b instead.  For the calls that direct_applies to.
-bool direct_applies(ElemType et, const CsCombineArgs &g);
+// amax_b instead.  For the calls that direct_applies to (scale_rules.h).
+bool direct_applies(ElemType et, bool cs, const CsCombineArgs &g);
 hipError_t launch_exponents_direct(ElemType et, bool cs, const CsCombineArgs &g, unsigned long long *amax_a,
                                    unsigned long long *amax_b, hipStream_t st);
 // K2: quantize + residues + 2M pre into operand planes.

@@ -1,0 +1,57 @@
+// K1: which calls find their exponents straight from the operands
+// (exponents_direct, k_scale.hip), and in which of its forms.
+#pragma once
+
+#include <stddef.h>
+
+namespace o2m {
+
+// Entries of an operand row that a thread holds in registers between the
+// maximum and the Cauchy-Schwarz sum: rows of up to 64 times as many.
+constexpr int kHold = 16;
+constexpr long kDirectK = 16384;                     // entries per operand row, both sources
+constexpr size_t kDirectBytes = size_t(72) << 20;    // of both operands
+constexpr long kDirectRowsCs = 16384, kDirectRowsPerColumnCs = 16;
+constexpr long kDirectRowsMax = 24576, kDirectRowsPerColumnMax = 4;
+constexpr long kDirectRowsTwo = 4096;                // Cauchy-Schwarz rule, two sources
+
+// Entries held per thread, 64 threads to a row: 1, 4, 8 or 16 (each its own
+// form of the kernel, so that a short row costs no more than its own rounds),
+// or 0 for a row that is read again: one longer than all of these, or one
+// with two sources (rank-2k updates).
+inline int direct_hold(long k, bool two_sources) {
+    if (two_sources || k > 64 * kHold) return 0;
+    return k <= 64 ? 1 : k <= 256 ? 4 : k <= 512 ? 8 : kHold;
+}
+
+// rows: operand rows that are rows of a column-major matrix (of A, or of a
+// transposed B); cols: those that are its columns.
+//
+// The direct kernel takes calls whose operands the caches can hold for its
+// second reading (2048 x 2048 x 1024, 64 MiB: 21.4 us against the chunked
+// scans' 31.2; 1500 x 1500 x 2000, 92 MiB: 39.8 against 39.5; 2048^3, 128 MiB:
+// 52.7 against 45.7), up to a row length where a workgroup's walk along its
+// rows alone evens out with the scans' parallel chunks (64 x 64 x 16000: 68.4
+// against 72.4; 300 x 300 x 4096: 23.2 against 33.6).
+//
+// It spends a wave's 64 lanes on every operand row however short, where a row
+// scan gives one lane of a wave to each of 64 rows: many rows go to the scans.
+// Columns count the other way, since the column scans spend 256 threads on
+// each.  (Scale phase in us, direct against the scans, m x n x k complex fp64,
+// fp32 in brackets.  Cauchy-Schwarz rule: 16384 x 1 x 16 10.6 and 11.0 (12.6,
+// 11.1), 16384 x 1 x 300 fp32 19.3, 18.5, 65536 x 1 x 16 25.4 and 17.8 (32.3,
+// 16.8); 65536 x 2048 x 16 28.4 and 23.9 (33.6, 22.9), 65536 x 8192 x 16 31.2
+// and 38.9 (39.0, 40.2), 131072 x 8192 x 16 54.8 and 91.8 (74.5, 102).  Max
+// rule: 24576 x 1 x 16 10.3 and 14.3 (13.9, 15.0), 65536 x 1 x 16 17.3 and 15.9
+// (25.2, 15.2), 65536 x 8192 x 16 22.5 and 26.1 (31.3, 25.3).  Rank-2k updates
+// under the Cauchy-Schwarz rule, whose two sources are both read again: ZHER2K
+// 8192 x 16 12.0 and 11.9, 8192 x 64 21.1 and 15.6.)
+inline bool direct_rule(size_t entry_bytes, bool cs, long k, bool two_sources, long rows, long cols) {
+    const size_t per_row = (size_t)k * (two_sources ? 2 : 1);
+    const size_t bytes = entry_bytes * per_row * ((size_t)rows + (size_t)cols);
+    const long most = !cs ? kDirectRowsMax + kDirectRowsPerColumnMax * cols
+                    : two_sources ? kDirectRowsTwo : kDirectRowsCs + kDirectRowsPerColumnCs * cols;
+    return per_row <= (size_t)kDirectK && bytes <= kDirectBytes && rows <= most;
+}
+
+}  // namespace o2m

@@ -133,12 +133,15 @@ def _special(x, rule):
 
 
 # The direct kernel takes 4 rows per workgroup, 8 from 960 rows and 16 from 1920
-# (not complex fp64 with k <= 1024), 64 entries of a row per round, 16 rounds
-# held in registers (k <= 1024), and calls up to 16384 entries per row; past
-# that the chunked scans run.
+# (not complex fp64 with k <= 1024), 64 entries of a row per round, 1, 4, 8 or
+# 16 rounds held in registers (k <= 64, 256, 512, 1024), and calls up to 16384
+# entries per row, 16384 + 16 n rows (Cauchy-Schwarz) and 24576 + 4 n (max);
+# past that the chunked scans run.
 @pytest.mark.parametrize("rule", ["max", "cs"])
 @pytest.mark.parametrize("m,n,k", [(1, 1, 1), (15, 17, 63), (16, 16, 64), (17, 15, 65), (33, 31, 1024), (18, 20, 1025),
-                                   (700, 263, 20), (959, 964, 9), (1915, 18, 1026), (6, 7, 16384), (7, 6, 16385), (2, 2, 0)])
+                                   (700, 263, 20), (959, 964, 9), (1915, 18, 1026), (6, 7, 16384), (7, 6, 16385), (2, 2, 0),
+                                   (17, 6, 256), (6, 17, 257), (18, 5, 512), (5, 18, 513),
+                                   (16416, 2, 3), (16417, 2, 3), (24584, 2, 3), (24585, 2, 3)])
 def test_exponents(o2m, m, n, k, rule):
     a = _special(W.complex_matrix(m, k, 41, dist="phi", phi=2.0), rule) if k else np.zeros((m, 0), np.complex128)
     b = _special(W.complex_matrix(n, k, 42, dist="phi", phi=2.0), rule).T if k else np.zeros((0, n), np.complex128)
@@ -172,6 +175,18 @@ def test_exponents_symmetric(o2m, n, k, rule):
                      (o2m.dsyrk_2m(to_dev(ra), scaling=rule), O.oq_dsyrk(ra, 16, scaling=rule)),
                      (o2m.dsyr2k_2m(to_dev(ra), to_dev(rb), scaling=rule), O.oq_dsyr2k(ra, rb, 16, scaling=rule))):
         assert same_bits(host(got)[tri], np.asarray(ref)[tri])
+
+
+@pytest.mark.parametrize("n", [4096, 4097])
+def test_exponents_many_rows_of_two_sources(o2m, n):
+    """Up to 4096 rows the direct kernel, more the row scans (Cauchy-Schwarz)."""
+    k = 5
+    a, b = (_special(W.complex_matrix(n, k, s, dist="phi", phi=1.0), "max") for s in (53, 54))
+    got = host(o2m.zher2k_2m(to_dev(a), to_dev(b), scaling="cs"))
+    rng = np.random.default_rng(n)
+    ent = [(0, 0), (n - 1, 0), (n - 1, n - 1), (2, 1)]
+    ent += [(max(i, j), min(i, j)) for i, j in rng.integers(0, n, (300, 2)).tolist()]
+    assert same_bits(np.array([got[i, j] for i, j in ent]), O.oq_zher2k(a, b, 16, entries=ent, scaling="cs"))
 
 
 @pytest.mark.parametrize("k", [40, 1030, 16390])

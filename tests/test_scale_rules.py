@@ -1,0 +1,54 @@
+"""Host build of the choice of K1's kernels (scale_rules.h): what a short row
+costs the direct kernel, and that many such rows are left to the scans."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    out = tmp_path_factory.mktemp("rules") / "libscale_rules_host.so"
+    subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", "-fPIC", "-shared",
+                    os.path.join(HERE, "scale_rules_host.cpp"), "-o", str(out)], check=True)
+    L = ctypes.CDLL(str(out))
+    I, Lg = ctypes.c_int, ctypes.c_long
+    L.t_direct_hold.argtypes = [Lg, I]
+    L.t_direct_rule.argtypes = [Lg, I, Lg, I, Lg, Lg]
+    return L
+
+
+def test_held_entries_follow_the_row(lib):
+    """A held form covers the row (64 threads to a row), and beyond the shortest
+    it is less than four times as long; longer rows and two sources are read
+    again."""
+    for k in range(1025):
+        h = lib.t_direct_hold(k, 0)
+        assert h in (1, 4, 8, 16) and 64 * h >= k
+        assert h == 1 or 64 * h < 4 * k
+        assert lib.t_direct_hold(k, 1) == 0
+    assert lib.t_direct_hold(1025, 0) == 0
+
+
+# entry bytes, Cauchy-Schwarz rule, k, two sources, row-mode rows, columns
+DIRECT = [(16, 1, 200, 0, 96, 80), (16, 0, 777, 0, 500, 333), (16, 1, 1024, 0, 1024, 1024), (8, 0, 2051, 0, 1537, 1283),
+          (16, 1, 16, 0, 16384, 1), (16, 0, 16, 0, 24576, 0), (8, 1, 64, 0, 65536, 8192), (16, 1, 64, 0, 32, 65536),
+          (8, 0, 16384, 0, 4, 0), (16, 1, 64, 1, 4096, 0), (16, 0, 64, 1, 16384, 0), (8, 0, 0, 0, 5, 7)]
+SCANS = [(16, 1, 16, 0, 262144, 32), (16, 0, 16, 0, 262144, 32), (8, 1, 16, 0, 262144, 32), (8, 1, 64, 0, 65536, 32),
+         (16, 1, 8, 0, 65536, 2048), (8, 0, 32, 0, 65536, 64), (16, 1, 64, 1, 8192, 0), (8, 1, 64, 1, 16384, 0),
+         (8, 0, 0, 0, 1 << 27, 1), (16, 1, 16385, 0, 4, 4), (16, 0, 8193, 1, 4, 0), (16, 0, 2048, 0, 2048, 2048)]
+
+
+@pytest.mark.parametrize("case", DIRECT)
+def test_direct_calls(lib, case):
+    assert lib.t_direct_rule(*case) == 1
+
+
+@pytest.mark.parametrize("case", SCANS)
+def test_scanned_calls(lib, case):
+    """Many short rows (a wave each in the direct kernel, a lane in the row
+    scans), long rows, operands beyond the caches."""
+    assert lib.t_direct_rule(*case) == 0
