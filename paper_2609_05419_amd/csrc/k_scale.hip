@@ -717,40 +717,29 @@ static void launch_cs_scan_t(const ScanArgs &a, int cpt, bool nt, bool two, unsi
     else launch_cs_scan_cpt<ET, PAIRS, false, false>(a, cpt, grid, st);
 }
 
-// What a scan's operands must share to go out in one launch.
-struct ScanKind {
-    int cpt;           // columns per thread in row mode (column mode: 4, the least)
-    bool pairs, nt;
-};
-static ScanKind scan_kind(ElemType et, const CsScan &s) {
-    // column chunks start at even rows: an even ld and a 16-byte aligned base align every pair
-    return {s.mode == 0 ? cs_row_cpt(s.rows, s.cols) : 4,
-            et == kF32 && s.mode == 1 && s.ld % 2 == 0 && ((uintptr_t)s.X & 15) == 0, streams(et, s.rows, s.cols)};
+// Workgroups of a scan along its rows or columns (x) and over their chunks (y).
+static dim3 scan_grid(const CsScan &s) {
+    if (s.mode != 0) return dim3((unsigned)s.cols, (unsigned)((s.rows + kColChunk - 1) / kColChunk));
+    const int w = 4 * cs_row_cpt(s.rows, s.cols);
+    return dim3((unsigned)((s.rows + 63) / 64), (unsigned)((s.cols + w - 1) / w));
 }
 
-constexpr size_t kBesideBytes = size_t(16) << 20;   // an operand that may adapt to the other
+static ScanShape scan_shape(ElemType et, const CsScan &s) {
+    const dim3 g = scan_grid(s);
+    // column chunks start at even rows: an even ld and a 16-byte aligned base align every pair
+    return {s.mode, s.mode == 0 ? cs_row_cpt(s.rows, s.cols) : 4,
+            et == kF32 && s.mode == 1 && s.ld % 2 == 0 && ((uintptr_t)s.X & 15) == 0, streams(et, s.rows, s.cols),
+            entry_bytes(et) * (size_t)s.rows * s.cols, (long)g.x * g.y};
+}
 
 hipError_t launch_cs_scan(ElemType et, int count, const CsScan *src, hipStream_t st) {
     if (count < 1 || count > 2) return hipErrorInvalidValue;
     if (src[0].rows <= 0 || src[0].cols <= 0) return count == 2 ? launch_cs_scan(et, 1, src + 1, st) : hipSuccess;
-    ScanKind k = scan_kind(et, src[0]);
+    ScanShape k = scan_shape(et, src[0]);
     if (count == 2) {
         const CsScan &s1 = src[1];
-        const ScanKind k1 = scan_kind(et, s1);
-        const size_t b0 = entry_bytes(et) * (size_t)src[0].rows * src[0].cols;
-        const size_t b1 = entry_bytes(et) * (size_t)s1.rows * s1.cols;
-        const size_t small = b0 < b1 ? b0 : b1;
-        bool fits;
-        if (src[0].mode != s1.mode) {
-            // a row scan of 32 columns per thread takes registers that a large
-            // column scan is better off without
-            fits = (k.cpt < 32 && k1.cpt < 32) || (src[0].mode == 1 ? b0 : b1) < kBesideBytes;
-        } else {
-            fits = src[0].mode == 0 ? k.cpt == k1.cpt : k.pairs == k1.pairs;
-        }
-        // a small operand may go past the caches along with a large one
-        fits = fits && (k.nt == k1.nt || small < kBesideBytes);
-        if (s1.rows <= 0 || s1.cols <= 0 || !fits) {
+        const ScanShape k1 = scan_shape(et, s1);
+        if (s1.rows <= 0 || s1.cols <= 0 || !scans_together(k, k1)) {
             const hipError_t e = launch_cs_scan(et, 1, src, st);
             return e != hipSuccess ? e : launch_cs_scan(et, 1, src + 1, st);
         }
@@ -763,12 +752,10 @@ hipError_t launch_cs_scan(ElemType et, int count, const CsScan *src, hipStream_t
     long blocks = 0;
     for (int i = 0; i < count; ++i) {
         const CsScan &s = src[i];
-        const unsigned nx = s.mode == 0 ? (unsigned)((s.rows + 63) / 64) : (unsigned)s.cols;
-        const int w = 4 * (s.mode == 0 ? cs_row_cpt(s.rows, s.cols) : 1);
-        const unsigned ny = (unsigned)(s.mode == 0 ? (s.cols + w - 1) / w : (s.rows + kColChunk - 1) / kColChunk);
-        a.src[i] = {s.X, s.rows, s.cols, s.ld, s.mode, s.chunk_ofs, s.p, nx, ny};
-        if (i == 0) a.blocks0 = nx * ny;
-        blocks += (long)nx * ny;
+        const dim3 g = scan_grid(s);
+        a.src[i] = {s.X, s.rows, s.cols, s.ld, s.mode, s.chunk_ofs, s.p, g.x, g.y};
+        if (i == 0) a.blocks0 = g.x * g.y;
+        blocks += (long)g.x * g.y;
     }
     if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
     const unsigned n = (unsigned)blocks;

@@ -1,5 +1,6 @@
 // K1: which calls find their exponents straight from the operands
-// (exponents_direct, k_scale.hip), and in which of its forms.
+// (exponents_direct, k_scale.hip), and in which of its forms; which scans of
+// two operands go out in one launch.
 #pragma once
 
 #include <stddef.h>
@@ -52,6 +53,34 @@ inline bool direct_rule(size_t entry_bytes, bool cs, long k, bool two_sources, l
     const long most = !cs ? kDirectRowsMax + kDirectRowsPerColumnMax * cols
                     : two_sources ? kDirectRowsTwo : kDirectRowsCs + kDirectRowsPerColumnCs * cols;
     return per_row <= (size_t)kDirectK && bytes <= kDirectBytes && rows <= most;
+}
+
+// One operand of a chunked scan (cs_scan_kernel).
+struct ScanShape {
+    int mode;              // 0: rows of a column-major matrix, 1: its columns
+    int cpt;               // columns per thread in row mode (column mode: 4, the least)
+    bool pairs, nt;        // 16-byte pairs, non-temporal loads
+    size_t bytes;          // of the operand
+    long groups;           // workgroups
+};
+constexpr size_t kBesideBytes = size_t(16) << 20;   // an operand that may adapt to the other
+constexpr long kBesideGroups = 2048;
+
+// Whether the scans of a and b can share a launch, and gain by it.  The kernel
+// of a row scan of 32 columns per thread holds two workgroups per CU; a column
+// scan beside it is held to as many.  That suits a small one (scale phase
+// together and apart: 4096 x 96 x 4096 64.1 and 68.5 us, 150000 x 2000 x 64 75.7
+// and 77.5), but not a large operand, nor one of many short columns (150000 x
+// 3000 x 64 80.8 and 80.1, 150000 x 8192 x 64 106 and 92.5).
+inline bool scans_together(const ScanShape &a, const ScanShape &b) {
+    if (a.mode == b.mode) {
+        if (a.mode == 0 ? a.cpt != b.cpt : a.pairs != b.pairs) return false;
+    } else if (a.cpt >= 32 || b.cpt >= 32) {
+        const ScanShape &c = a.mode == 1 ? a : b;
+        if (c.bytes >= kBesideBytes || c.groups > kBesideGroups) return false;
+    }
+    // a small operand may go past the caches along with a large one
+    return a.nt == b.nt || (a.bytes < b.bytes ? a.bytes : b.bytes) < kBesideBytes;
 }
 
 }  // namespace o2m

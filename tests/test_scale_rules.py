@@ -1,5 +1,6 @@
 """Host build of the choice of K1's kernels (scale_rules.h): what a short row
-costs the direct kernel, and that many such rows are left to the scans."""
+costs the direct kernel, that many such rows are left to the scans, and which
+scans share a launch."""
 import ctypes
 import os
 import subprocess
@@ -18,6 +19,7 @@ def lib(tmp_path_factory):
     I, Lg = ctypes.c_int, ctypes.c_long
     L.t_direct_hold.argtypes = [Lg, I]
     L.t_direct_rule.argtypes = [Lg, I, Lg, I, Lg, Lg]
+    L.t_scans_together.argtypes = [ctypes.POINTER(Lg)] * 2
     return L
 
 
@@ -52,3 +54,20 @@ def test_scanned_calls(lib, case):
     """Many short rows (a wave each in the direct kernel, a lane in the row
     scans), long rows, operands beyond the caches."""
     assert lib.t_direct_rule(*case) == 0
+
+
+MB = 1 << 20
+ROWS32, ROWS16 = (0, 32, 0, 1, 256 * MB, 2048), (0, 16, 0, 0, 64 * MB, 2048)
+# rows beside columns, row scans, column scans; the smaller of two loads follows
+TOGETHER = [(ROWS32, (1, 4, 0, 0, 6 * MB, 192)), (ROWS32, (1, 4, 0, 0, 2 * MB, 2048)), (ROWS16, (1, 4, 0, 0, 64 * MB, 8192)),
+            ((1, 4, 1, 0, 6 * MB, 192), ROWS32), (ROWS32, (0, 32, 0, 1, 200 * MB, 4096)), (ROWS16, ROWS16),
+            ((1, 4, 1, 0, 20 * MB, 99), (1, 4, 1, 0, 40 * MB, 99)), ((1, 4, 0, 1, 200 * MB, 99), (1, 4, 0, 0, 15 * MB, 99))]
+APART = [(ROWS32, (1, 4, 0, 0, 2 * MB, 2049)), ((1, 4, 0, 0, 8 * MB, 8192), ROWS32),      # many short columns
+         (ROWS32, (1, 4, 0, 0, 16 * MB, 512)), (ROWS32, ROWS16), ((1, 4, 1, 0, 20 * MB, 99), (1, 4, 0, 0, 20 * MB, 99)),
+         (ROWS16, (1, 4, 0, 1, 200 * MB, 99))]
+
+
+@pytest.mark.parametrize("a,b,want", [(*c, 1) for c in TOGETHER] + [(*c, 0) for c in APART])
+def test_scans_of_two_operands(lib, a, b, want):
+    v = ctypes.c_long * 6
+    assert lib.t_scans_together(v(*a), v(*b)) == want
