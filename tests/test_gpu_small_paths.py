@@ -96,22 +96,29 @@ def test_residue_edges_symmetric(o2m, n, k, N, rule):
 @pytest.mark.parametrize("n,k", [(1, 3), (31, 5), (32, 8), (33, 7), (530, 4)])
 def test_fresh_symmetric_output_is_zero_elsewhere(o2m, n, k, uplo):
     """The whole fresh output: the triangle as the oracle has it, +0 in the
-    other one, though the memory it is given held NaN.  Sizes around a 32 x 32
-    tile and beyond one super-tile (512)."""
+    other one, though the memory held NaN; through the binding, and into a
+    buffer of NaN with ldc = n + 3, whose rows beyond n stay as they were.
+    Sizes around a 32 x 32 tile and beyond one super-tile (512)."""
     a, b = (W.complex_matrix(n, k, s, dist="phi", phi=0.5) for s in (81, 82))
     ra, rb = (W.real_matrix(n, k, s, dist="phi", phi=0.5) for s in (83, 84))
-    for call, ref, dt in ((lambda: o2m.zherk_2m(to_dev(a), uplo=uplo), O.oq_zherk(a, 16), np.complex128),
-                          (lambda: o2m.dsyrk_2m(to_dev(ra), uplo=uplo), O.oq_dsyrk(ra, 16), np.float64),
-                          (lambda: o2m.zher2k_2m(to_dev(a), to_dev(b), uplo=uplo), O.oq_zher2k(a, b, 16), np.complex128),
-                          (lambda: o2m.dsyr2k_2m(to_dev(ra), to_dev(rb), uplo=uplo), O.oq_dsyr2k(ra, rb, 16), np.float64)):
-        dirty = torch.full((n, n), float("nan"), dtype=torch.from_numpy(np.zeros(1, dt)).dtype, device=DEV)
-        del dirty                                  # the allocator hands the block to the output
-        got = host(call())
+    dev = {"h": (to_dev(a),), "s": (to_dev(ra),), "x": (to_dev(a), to_dev(b)), "y": (to_dev(ra), to_dev(rb))}
+    for op, call, ref, dt in (("h", o2m.zherk_2m, O.oq_zherk(a, 16), np.complex128),
+                              ("s", o2m.dsyrk_2m, O.oq_dsyrk(ra, 16), np.float64),
+                              ("x", o2m.zher2k_2m, O.oq_zher2k(a, b, 16), np.complex128),
+                              ("y", o2m.dsyr2k_2m, O.oq_dsyr2k(ra, rb, 16), np.float64)):
+        buf = torch.full((n, n + 3), float("nan"), dtype=dev[op][0].dtype, device=DEV)
+        A, B = dev[op][0], dev[op][-1]
+        st = o2m._L.o2m_sym_fresh(op.encode(), uplo.encode(), n, k, A.data_ptr(), n, B.data_ptr(), n, buf.data_ptr(),
+                                  n + 3, 16, 0, torch.cuda.current_stream().cuda_stream)
+        assert st == 0
+        torch.cuda.synchronize()
+        assert torch.isnan(buf[:, n:].real).all()
         low = np.tril(np.asarray(ref))             # the oracle's lower triangle
         want = low if uplo == "L" else np.triu(low.conj().T)
         keep = np.tril(np.ones((n, n), bool)) if uplo == "L" else np.triu(np.ones((n, n), bool))
-        assert np.array_equal(got[keep], want[keep])
-        assert same_bits(got[~keep], np.zeros(int((~keep).sum()), dt))
+        for got in (host(buf[:, :n].t()), host(call(*dev[op], uplo=uplo))):
+            assert np.array_equal(got[keep], want[keep])
+            assert same_bits(got[~keep], np.zeros(int((~keep).sum()), dt))
 
 
 # ------------------------------------------------------------------ exponents
