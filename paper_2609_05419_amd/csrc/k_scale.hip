@@ -679,16 +679,6 @@ hipError_t launch_exponents(int ca, const unsigned long long *amax_a, int32_t *E
     return hipGetLastError();
 }
 
-// Columns per thread of the row-mode scan: 32 (a workgroup covers 64 rows x
-// 128 columns), fewer (down to 4) when the grid would otherwise hold fewer
-// than ~2048 workgroups (small matrices).
-int cs_row_cpt(int rows, int cols) {
-    const long rb = (rows + 63) / 64;
-    int cpt = 32;
-    while (cpt > 4 && rb * ((cols + 4 * cpt - 1) / (4 * cpt)) < 2048) cpt >>= 1;
-    return cpt;
-}
-
 int cs_chunks(int mode, int rows, int cols) {
     if (rows <= 0 || cols <= 0) return 0;
     if (mode == 0) {

@@ -55,6 +55,16 @@ inline bool direct_rule(size_t entry_bytes, bool cs, long k, bool two_sources, l
     return per_row <= (size_t)kDirectK && bytes <= kDirectBytes && rows <= most;
 }
 
+// Columns per thread of the row-mode scan: 32 (a workgroup covers 64 rows x
+// 128 columns), fewer (down to 4) when the grid would otherwise hold fewer
+// than ~2048 workgroups (small matrices).
+inline int cs_row_cpt(int rows, int cols) {
+    const long rb = (rows + 63) / 64;
+    int cpt = 32;
+    while (cpt > 4 && rb * ((cols + 4 * cpt - 1) / (4 * cpt)) < 2048) cpt >>= 1;
+    return cpt;
+}
+
 // One operand of a chunked scan (cs_scan_kernel).
 struct ScanShape {
     int mode;              // 0: rows of a column-major matrix, 1: its columns

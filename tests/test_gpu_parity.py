@@ -15,6 +15,7 @@ import pytest
 import oracle as O
 import workloads as W
 from conftest import same_bits
+from scale_shapes import RESUMMED_K
 
 pytestmark = pytest.mark.gpu
 
@@ -588,8 +589,10 @@ def _offset_view(x, pad_rows, offset):
 
 # complex fp32 entries are read two per 16-byte load when every pair is
 # aligned (even leading dimension, aligned base): consecutive entries of a
-# column of B, rows 2i, 2i + 1 of A; one entry per load otherwise
-PAIR_CASES = [(41, 33, 11, 0), (41, 33, 10, 0), (40, 33, 11, 1), (41, 4101, 3, 0), (40, 4101, 4, 1), (257, 300, 5, 0)]
+# column of B, rows 2i, 2i + 1 of A; one entry per load otherwise.  The residues
+# of all of these read so, the scaling from k = 16385 on (Cauchy-Schwarz rule)
+PAIR_CASES = [(41, 33, 11, 0), (41, 33, 10, 0), (40, 33, 11, 1), (41, 4101, 3, 0), (40, 4101, 4, 1), (257, 300, 5, 0),
+              (41, 16385, 11, 0), (40, 16386, 10, 0), (41, 16387, 10, 0), (40, 16385, 11, 1)]
 
 
 @pytest.mark.parametrize("rule", ["max", "cs"])
@@ -785,18 +788,20 @@ def test_zgemm_in_a_hip_graph(o2m):
     _graph_replays(o2m, 300, 270, 520, 16, seeds=(9401, 9403, 9405))
 
 
-def test_zgemm_cs_in_a_hip_graph(o2m):
-    """The Cauchy-Schwarz rule's one-pass scaling is capturable too, including
-    the rows its chunk records leave open (summed again inside the graph): the
-    second replay holds two such rows, the third none."""
+@pytest.mark.parametrize("m,n,k", [(300, 270, 520), (40, 36, RESUMMED_K)])
+def test_zgemm_cs_in_a_hip_graph(o2m, m, n, k):
+    """The Cauchy-Schwarz rule's scaling is capturable too, summed from the data
+    (k = 520) and in one pass over chunks, including the rows whose records
+    leave the exponent open (summed again inside the graph): the second replay
+    holds two such rows, the third none."""
     from cs_inputs import straddle_vector
 
     def edit(seed, a):
         if seed == 9423:
             a[5, :] = straddle_vector(a.shape[1], "low")
-            a[200, :] = straddle_vector(a.shape[1], "high")
-    print("[parity] graph replays 300x270x520 N=16, Cauchy-Schwarz rule", flush=True)
-    _graph_replays(o2m, 300, 270, 520, 16, seeds=(9421, 9423, 9425), scaling="cs", edit=edit)
+            a[m - 1, :] = straddle_vector(a.shape[1], "high")
+    print(f"[parity] graph replays {m}x{n}x{k} N=16, Cauchy-Schwarz rule", flush=True)
+    _graph_replays(o2m, m, n, k, 16, seeds=(9421, 9423, 9425), scaling="cs", edit=edit)
 
 
 @pytest.mark.slow
@@ -952,12 +957,14 @@ def test_zgemm_op_4096_sampled(o2m, ta, tb, rule):
     assert ok
 
 
-def test_cs_resummed_entries_transposed_operands(o2m):
+@pytest.mark.parametrize("k", [4096, RESUMMED_K])
+def test_cs_resummed_entries_transposed_operands(o2m, k):
     """Rows of op(A) read as columns of the stored A, columns of op(B) read as
     rows of the stored B, among them ones whose chunk records leave the
-    Cauchy-Schwarz exponent open (summed again from the data)."""
+    Cauchy-Schwarz exponent open (summed again from the data) where the scans
+    run (the longer k)."""
     from cs_inputs import straddle_vector
-    m, n, k, N = 24, 20, 4096, 16
+    m, n, N = 24, 20, 16
     opa = W.complex_matrix(m, k, 4731, dist="phi", phi=0.5)
     opb = W.complex_matrix(k, n, 4732, dist="phi", phi=0.5)
     for i, kind in ((2, "low"), (m - 1, "high")):      # a column of the stored A: chunks of 2048

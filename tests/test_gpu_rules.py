@@ -10,6 +10,7 @@ import pytest
 import oracle as O
 import workloads as W
 from conftest import same_bits
+from scale_shapes import RESUMMED_K, RESUMMED_K_RANK2
 
 pytestmark = pytest.mark.gpu
 
@@ -287,7 +288,9 @@ def test_zher2k_4096_sampled(o2m):
 # ------------------------------- one pass over each operand: re-summed entries
 # Rows (columns) built so that the per-chunk records of the one-pass scan do
 # not settle the exponent (tests/cs_inputs.py): the library sums them again
-# from the data, and everything must still equal the oracle bit for bit.
+# from the data, and everything must still equal the oracle bit for bit.  The
+# scans run at the longer k of each test; at the shorter one the same vectors
+# go through the kernel that sums every row from the data.
 
 
 def _straddle_operands(m, n, k, dtype=np.complex128):
@@ -303,8 +306,9 @@ def _straddle_operands(m, n, k, dtype=np.complex128):
     return a.astype(dtype), b.astype(dtype), rows, cols
 
 
-def test_cs_resummed_entries_exponents_and_zgemm(o2m):
-    m, n, k, N = 40, 36, 4096, 16
+@pytest.mark.parametrize("k", [4096, RESUMMED_K])
+def test_cs_resummed_entries_exponents_and_zgemm(o2m, k):
+    m, n, N = 40, 36, 16
     a, b, rows, cols = _straddle_operands(m, n, k)
     _, E, F = o2m.zgemm_2m_residues(to_dev(a), to_dev(b), n_moduli=N, scaling="cs")
     E0, _, F0, _ = O.exponents(a, b, "cs")
@@ -321,15 +325,17 @@ def test_cs_resummed_entries_exponents_and_zgemm(o2m):
     assert ok_e and ok
 
 
-def test_cs_resummed_entries_cgemm(o2m):
-    a, b, _, _ = _straddle_operands(24, 20, 4096, np.complex64)
+@pytest.mark.parametrize("k", [4096, RESUMMED_K])
+def test_cs_resummed_entries_cgemm(o2m, k):
+    a, b, _, _ = _straddle_operands(24, 20, k, np.complex64)
     ref = O.oq_cgemm(a, b, 8, scaling="cs")
     assert same_bits(host(o2m.cgemm_2m(to_dev(a), to_dev(b), n_moduli=8, scaling="cs")), ref)
 
 
-def test_cs_resummed_rows_symmetric_calls(o2m):
+@pytest.mark.parametrize("k", [700, RESUMMED_K_RANK2, RESUMMED_K])
+def test_cs_resummed_rows_symmetric_calls(o2m, k):
     from cs_inputs import straddle_vector
-    n, k, N = 30, 700, 16
+    n, N = 30, 16
     a = W.complex_matrix(n, k, 193, dist="phi", phi=2.0)
     b = W.complex_matrix(n, k, 194, dist="phi", phi=2.0)
     for i, kind in ((0, "low"), (7, "high"), (n - 1, "high")):

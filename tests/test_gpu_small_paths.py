@@ -292,9 +292,9 @@ def test_crt_rows_gauss(o2m, m, n):
 
 
 # ------------------------------------------------------------------ chunked scans
-# Past the direct kernel's rows (16384): two operands in one launch (row scan
-# beside column scan, two row scans, two column scans, rank-2k), and apart
-# (column pairs of one fp32 operand only).
+# Past the direct kernel's rows (16384), with 4 columns per thread in the row
+# scans: two operands in one launch (row scan beside column scan, two row scans,
+# two column scans), and apart (column pairs of one fp32 operand only).
 @pytest.mark.parametrize("call,m,n,k,ta,tb,pad", [("z", 7, 9, 16390, "N", "N", (0, 0)), ("z", 9, 7, 16385, "N", "T", (1, 1)),
                                                   ("z", 6, 65, 16401, "T", "N", (0, 2)), ("z", 65, 6, 16400, "C", "T", (1, 0)),
                                                   ("c", 8, 6, 16386, "N", "N", (0, 0)), ("c", 7, 9, 16387, "T", "N", (1, 1)),
@@ -307,3 +307,38 @@ def test_scans_of_two_operands(o2m, call, m, n, k, ta, tb, pad):
     fn, ref = (o2m.cgemm_2m_op, O.oq_cgemm) if call == "c" else (o2m.zgemm_2m_op, O.oq_zgemm)
     got = host(fn(padded(A, pad[0]), padded(B, pad[1]), ta, tb, n_moduli=16, scaling="cs"))
     assert same_bits(got, ref(a, b, 16, scaling="cs"))
+
+
+def _scan_sizes():
+    from scale_shapes import SCANS
+    return [c[:6] for c in SCANS]
+
+
+@pytest.mark.parametrize("call,m,n,k,ta,tb", _scan_sizes())
+def test_scans_by_columns_per_thread(o2m, call, m, n, k, ta, tb):
+    """Operands beyond the caches: every number of columns per thread of the
+    row scan, beside a column scan and a row scan, with plain and non-temporal
+    loads (test_scale_rules checks that these sizes take them).  All exponents,
+    where the hook gives them, and sampled entries, among them the rows and
+    columns that the records leave open."""
+    from cs_inputs import straddle_vector
+    dt = np.complex64 if call == "c" else np.complex128
+    a = W.complex_matrix(m, k, 13, dist="phi", phi=1.0).astype(dt)
+    b = W.complex_matrix(k, n, 14, dist="phi", phi=1.0).astype(dt)
+    wide = dict(exact=(0, 2048), binade=(2048, 2112), stride=2048)     # chunks of 2048 along a column
+    if k > 2112:
+        a[7, :], a[m - 1, :] = (straddle_vector(k, s, dtype=dt, **({} if ta == "N" else wide)) for s in ("low", "high"))
+        b[:, 3], b[:, n - 1] = (straddle_vector(k, s, dtype=dt, **(wide if tb == "N" else {})) for s in ("high", "low"))
+    A, B = (to_dev(np.asfortranarray(op_of(x, t))) for x, t in ((a, ta), (b, tb)))
+    if call == "z" and ta == tb == "N":
+        _, E, F = o2m.zgemm_2m_residues(A, B, n_moduli=16, scaling="cs")
+        E0, _, F0, _ = O.exponents(a, b, "cs")
+        assert np.array_equal(E.cpu().numpy(), E0) and np.array_equal(F.cpu().numpy(), F0)
+    fn, ref = (o2m.cgemm_2m_op, O.oq_cgemm) if call == "c" else (o2m.zgemm_2m_op, O.oq_zgemm)
+    N = 8 if call == "c" else 16
+    got = fn(A, B, ta, tb, n_moduli=N, scaling="cs")
+    rng = np.random.default_rng(m)
+    ent = [(i, j) for i in (0, 7, m - 1) for j in (0, 3, n - 1)]
+    ent += [(int(i), int(j)) for i, j in zip(rng.integers(0, m, 60), rng.integers(0, n, 60))]
+    idx = torch.tensor(ent, device=DEV)
+    assert same_bits(got[idx[:, 0], idx[:, 1]].cpu().numpy(), ref(a, b, N, entries=ent, scaling="cs"))

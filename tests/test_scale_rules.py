@@ -7,6 +7,8 @@ import subprocess
 
 import pytest
 
+from scale_shapes import RESUMMED_K, RESUMMED_K_RANK2, SCANS as SCANNED_SIZES
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 
 
@@ -19,6 +21,7 @@ def lib(tmp_path_factory):
     I, Lg = ctypes.c_int, ctypes.c_long
     L.t_direct_hold.argtypes = [Lg, I]
     L.t_direct_rule.argtypes = [Lg, I, Lg, I, Lg, Lg]
+    L.t_row_cpt.argtypes = [I, I]
     L.t_scans_together.argtypes = [ctypes.POINTER(Lg)] * 2
     return L
 
@@ -71,3 +74,18 @@ APART = [(ROWS32, (1, 4, 0, 0, 2 * MB, 2049)), ((1, 4, 0, 0, 8 * MB, 8192), ROWS
 def test_scans_of_two_operands(lib, a, b, want):
     v = ctypes.c_long * 6
     assert lib.t_scans_together(v(*a), v(*b)) == want
+
+
+@pytest.mark.parametrize("call,m,n,k,ta,tb,cpt,nt", SCANNED_SIZES)
+def test_sizes_of_the_scan_tests(lib, call, m, n, k, ta, tb, cpt, nt):
+    """The GPU tests of the scans reach them, in the form they name."""
+    e = 16 if call == "z" else 8
+    rows = (m if ta == "N" else 0) + (n if tb != "N" else 0)
+    assert lib.t_direct_rule(e, 1, k, 0, rows, m + n - rows) == 0
+    assert (lib.t_row_cpt(m, k) if ta == "N" else 0) == cpt
+    assert (e * m * k >= 128 << 20) == nt
+
+
+def test_sizes_of_the_resummed_tests(lib):
+    assert lib.t_direct_rule(8, 1, RESUMMED_K, 0, 1, 0) == 0
+    assert lib.t_direct_rule(8, 1, RESUMMED_K_RANK2, 1, 1, 0) == 0
