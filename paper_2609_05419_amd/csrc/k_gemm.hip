@@ -330,8 +330,10 @@ __device__ inline void edge_stage(v4i (&acc)[8][8], const Wave &w, int kb, int s
 // MFMAs and the 8 copies of stage `sstage` (= kb+4) of (sA, sB) into the
 // freed buffer every fourth one of the last 32.  The MFMAs walk the 8 x 8
 // blocks boustrophedon, so that each shares an operand fragment with the one
-// before it: the launch is held by its power draw, and the operand registers
-// toggle less (8192^3 N = 16: 11.51 -> 11.46 ms, smaller shapes level).
+// before it, for a launch held by its power draw: the operand registers toggle
+// less.  Worth 0.4% at 8192^3 (N = 16, in turn: 11.63 against 11.58 ms and 11.65
+// against 11.59; two runs of one build differ by 0.15% there), nothing that
+// shows at smaller shapes.
 template <bool FIRST = false>
 __device__ inline void steady_stage(v4i (&acc)[8][8], const Wave &w, int kb, const v4i (&ca)[8], const v4i (&cb)[8],
                                     v4i (&na)[8], v4i (&nb)[8], __amdgpu_buffer_rsrc_t sA,

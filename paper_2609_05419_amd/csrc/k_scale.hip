@@ -16,8 +16,9 @@
 // settles G, and sums the rare row whose bracket straddles a power of 4 again
 // from the data (cs_combine_kernel).
 //
-// Calls whose operands the caches hold take neither: exponents_direct finds
-// either rule's exponents of both operands in one launch.
+// Calls of few rows whose operands the caches hold take neither:
+// exponents_direct finds either rule's exponents of both operands in one launch
+// (scale_rules.h).
 //
 // Bound: HBM.  Algorithmic bytes = the matrix read once per pass (16 B per
 // complex fp64 element).  Rows of a column-major A are strided, so a thread owns one

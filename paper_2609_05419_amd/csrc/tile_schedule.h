@@ -42,9 +42,13 @@
 // strip is fetched by one or two XCDs only.  GEMM phase, N = 16, before ->
 // after: 1024^3 55 -> 43 us, 2048^3 249 -> 236, 1024 x 1024 x 65536 1702 -> 1448,
 // 500 x 333 x 777 26 -> 21; level at 144 and 256 tiles.  A single tile-row or
-// tile-column has no such neighbours (its long operand is read once either
-// way) and stays product-major while it fills the XCDs: 4096 x 96 x 4096 took
-// 132 us spread against 130.
+// tile-column of the 256 x 256 tile (129 to 256 output rows or columns; fewer
+// take a smaller tile, always spread) has no such neighbours: its long operand
+// is read once either way.  It stays product-major while it fills the XCDs:
+// 8192 x 256 x 1024 86 us against 92 spread, 4096 x 200 x 4096 131 against 136,
+// 8192 x 200 x 4096 248 against 255.  Past that k spread is the faster one
+// (4096 x 250 x 8192 243 against 228, 2500 x 200 x 30000 785 against 650),
+// which the plan does not use.
 #pragma once
 
 #ifndef O2M_HD
@@ -136,8 +140,11 @@ O2M_HD inline GemmSchedule gemm_schedule(int mt, int nt, int kblocks, int batch,
 // CU rounded up: `tile` is a tile's prologue and epilogue, `stage` a stage
 // with the CU full, `latency` what a stage costs however empty the CU is.  The
 // constants fit the GEMM phase of 30 shapes from 60^3 to 4096^3 measured with
-// each of the four (to 8-11%); the estimate's choice is the fastest or within
-// 7% of it on all of them.  A launch long enough to be held by its power draw
+// each of the four (to 8-11%, narrow panels apart); the estimate's choice is
+// the fastest or within 7% of it on all of them.  It has no term for operand
+// traffic, which is what a narrow panel costs: of 4096 x 96 x 4096 it says 104,
+// 66, 77 and 113 us for the four tiles, measured 129, 113, 116 and 163, in the
+// same order.  A launch long enough to be held by its power draw
 // pays for the extra data that the smaller tiles move: their stages cost up to
 // 16% more (`sustained`, by the large tile's estimate in units of 600 us; 3492
 // x 1543 x 16566 at N = 14: 2033 us with the large tile, 2312 with 256 x 128,
