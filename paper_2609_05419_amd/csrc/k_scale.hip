@@ -772,8 +772,9 @@ hipError_t launch_cs_combine(ElemType et, const CsCombineArgs &g, hipStream_t st
 }
 
 bool direct_applies(ElemType et, bool cs, const CsCombineArgs &g) {
-    const long rows = (g.amode == 0 ? g.ca : 0L) + (g.bmode == 0 ? g.cb : 0L);
-    return direct_rule(entry_bytes(et), cs, g.k, g.B2 != nullptr, rows, (long)g.ca + g.cb - rows);
+    const long ra = g.amode == 0 ? g.ca : 0, rb = g.bmode == 0 ? g.cb : 0;
+    return direct_rule(entry_bytes(et), cs, g.k, g.B2 != nullptr, ra + rb, ra > rb ? ra : rb,
+                       (long)g.ca + g.cb - ra - rb);
 }
 
 // Rows per workgroup: 16 once that gives kDirectGroups workgroups, half or a

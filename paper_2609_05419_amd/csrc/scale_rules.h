@@ -15,6 +15,7 @@ constexpr size_t kDirectBytes = size_t(72) << 20;    // of both operands
 constexpr long kDirectRowsCs = 16384, kDirectRowsPerColumnCs = 16;
 constexpr long kDirectRowsMax = 24576, kDirectRowsPerColumnMax = 4;
 constexpr long kDirectRowsTwo = 4096;                // Cauchy-Schwarz rule, two sources
+constexpr long kDirectColumnK = 3584;                // Cauchy-Schwarz rule, columns only
 
 // Entries held per thread, 64 threads to a row: 1, 4, 8 or 16 (each its own
 // form of the kernel, so that a short row costs no more than its own rounds),
@@ -25,8 +26,19 @@ inline int direct_hold(long k, bool two_sources) {
     return k <= 64 ? 1 : k <= 256 ? 4 : k <= 512 ? 8 : kHold;
 }
 
+// Columns per thread of the row-mode scan: 32 (a workgroup covers 64 rows x
+// 128 columns), fewer (down to 4) when the grid would otherwise hold fewer
+// than ~2048 workgroups (small matrices).
+inline int cs_row_cpt(int rows, int cols) {
+    const long rb = (rows + 63) / 64;
+    int cpt = 32;
+    while (cpt > 4 && rb * ((cols + 4 * cpt - 1) / (4 * cpt)) < 2048) cpt >>= 1;
+    return cpt;
+}
+
 // rows: operand rows that are rows of a column-major matrix (of A, or of a
-// transposed B); cols: those that are its columns.
+// transposed B), larger: of those, the ones of the operand that has more; cols:
+// those that are its columns.
 //
 // The direct kernel takes calls whose operands the caches can hold for its
 // second reading (2048 x 2048 x 1024, 64 MiB: 21.4 us against the chunked
@@ -47,22 +59,26 @@ inline int direct_hold(long k, bool two_sources) {
 // (25.2, 15.2), 65536 x 8192 x 16 22.5 and 26.1 (31.3, 25.3).  Rank-2k updates
 // under the Cauchy-Schwarz rule, whose two sources are both read again: ZHER2K
 // 8192 x 16 12.0 and 11.9, 8192 x 64 21.1 and 15.6.)
-inline bool direct_rule(size_t entry_bytes, bool cs, long k, bool two_sources, long rows, long cols) {
+//
+// Under the Cauchy-Schwarz rule, which reads a row of more than 1024 entries
+// twice, the scans are the faster ones in two more places (scale phase again).
+// Where a row scan has 8 columns per thread or more, and so half the records to
+// combine or fewer: DSYRK 1000 x 4000 23.7 and 28.8 (4 columns), 1500 x 3000
+// 29.7 and 21.7, 600 x 8000 45.3 and 30.1, ZHERK 1100 x 4100 34.8 and 28.3,
+// DSYR2K 800 x 5500 78.0 and 38.7; least from 1920 rows on, where the direct
+// kernel has 16 rows per workgroup (2000 x 3000 22.3 and 22.4, 3000 x 2500 30.9
+// and 24.8).  And between columns alone, whose chunks leave few records: 64 x
+// 64 x 2560 complex fp64 13.4 and 11.0, 4000 15.4 and 11.2, 16384 47.0 and 17.0;
+// fp32 64 x 64 x 4000 14.1 and 11.5, 1000 x 1000 x 4000 30.4 and 26.3, but 800 x
+// 800 x 3500 20.0 and 22.6.
+inline bool direct_rule(size_t entry_bytes, bool cs, long k, bool two_sources, long rows, long larger, long cols) {
     const size_t per_row = (size_t)k * (two_sources ? 2 : 1);
     const size_t bytes = entry_bytes * per_row * ((size_t)rows + (size_t)cols);
     const long most = !cs ? kDirectRowsMax + kDirectRowsPerColumnMax * cols
                     : two_sources ? kDirectRowsTwo : kDirectRowsCs + kDirectRowsPerColumnCs * cols;
+    if (cs && rows == 0 && k > kDirectColumnK) return false;
+    if (cs && larger > 0 && k > 64 * kHold && k <= kDirectK && cs_row_cpt((int)larger, (int)k) > 4) return false;
     return per_row <= (size_t)kDirectK && bytes <= kDirectBytes && rows <= most;
-}
-
-// Columns per thread of the row-mode scan: 32 (a workgroup covers 64 rows x
-// 128 columns), fewer (down to 4) when the grid would otherwise hold fewer
-// than ~2048 workgroups (small matrices).
-inline int cs_row_cpt(int rows, int cols) {
-    const long rb = (rows + 63) / 64;
-    int cpt = 32;
-    while (cpt > 4 && rb * ((cols + 4 * cpt - 1) / (4 * cpt)) < 2048) cpt >>= 1;
-    return cpt;
 }
 
 // One operand of a chunked scan (cs_scan_kernel).

@@ -3,8 +3,9 @@
 
 extern "C" {
 int t_direct_hold(long k, int two_sources) { return o2m::direct_hold(k, two_sources != 0); }
-int t_direct_rule(long entry_bytes, int cs, long k, int two_sources, long rows, long cols) {
-    return o2m::direct_rule((size_t)entry_bytes, cs != 0, k, two_sources != 0, rows, cols);
+int t_direct_rule(long entry_bytes, int cs, long k, int two_sources, long rows, long larger,
+                  long cols) {
+    return o2m::direct_rule((size_t)entry_bytes, cs != 0, k, two_sources != 0, rows, larger, cols);
 }
 int t_row_cpt(int rows, int cols) { return o2m::cs_row_cpt(rows, cols); }
 // v: mode, columns per thread, pairs, non-temporal, bytes, workgroups of either scan

@@ -1,4 +1,4 @@
-"""Sizes beyond the direct exponent kernel's, shared by the GPU tests of the
+"""Sizes that the direct exponent kernel leaves to the scans, shared by the GPU tests of the
 chunked scans and the host test of the rules that send them there."""
 
 # call, m, n, k, transa, transb, columns per thread of A's row scan (0: A is
@@ -12,6 +12,9 @@ SCANS = [
     ("c", 4099, 45, 4100, "N", "N", 32, True),        # pairs of fp32 columns
     ("c", 3001, 1001, 3002, "N", "N", 16, False),
     ("c", 2901, 1300, 2301, "T", "N", 0, False),      # two column scans, odd leading dimensions
+    ("z", 1101, 45, 4101, "N", "N", 8, False),        # within the caches, 8 columns per thread
+    ("z", 1101, 33, 4101, "N", "T", 8, False),        # the same, a small row scan apart
+    ("c", 45, 30, 3585, "T", "N", 0, False),          # long columns alone
 ]
 # k of rows that the scans' records leave open
 RESUMMED_K = 17000          # GEMM calls, ZHERK, DSYRK

@@ -143,7 +143,8 @@ def _special(x, rule):
 # (not complex fp64 with k <= 1024), 64 entries of a row per round, 1, 4, 8 or
 # 16 rounds held in registers (k <= 64, 256, 512, 1024), and calls up to 16384
 # entries per row, 16384 + 16 n rows (Cauchy-Schwarz) and 24576 + 4 n (max);
-# past that the chunked scans run.
+# past that the chunked scans run (Cauchy-Schwarz rule: also between columns
+# alone past 3584 entries, and where a row scan has 8 columns per thread).
 @pytest.mark.parametrize("rule", ["max", "cs"])
 @pytest.mark.parametrize("m,n,k", [(1, 1, 1), (15, 17, 63), (16, 16, 64), (17, 15, 65), (33, 31, 1024), (18, 20, 1025),
                                    (700, 263, 20), (959, 964, 9), (1915, 18, 1026), (6, 7, 16384), (7, 6, 16385), (2, 2, 0),
@@ -316,11 +317,11 @@ def _scan_sizes():
 
 @pytest.mark.parametrize("call,m,n,k,ta,tb", _scan_sizes())
 def test_scans_by_columns_per_thread(o2m, call, m, n, k, ta, tb):
-    """Operands beyond the caches: every number of columns per thread of the
-    row scan, beside a column scan and a row scan, with plain and non-temporal
-    loads (test_scale_rules checks that these sizes take them).  All exponents,
-    where the hook gives them, and sampled entries, among them the rows and
-    columns that the records leave open."""
+    """Every number of columns per thread of the row scan, beside a column scan
+    and a row scan, with plain and non-temporal loads, and long columns
+    (test_scale_rules checks that these sizes take them).  All exponents, where
+    the hook gives them, and sampled entries, among them the rows and columns
+    that the records leave open."""
     from cs_inputs import straddle_vector
     dt = np.complex64 if call == "c" else np.complex128
     a = W.complex_matrix(m, k, 13, dist="phi", phi=1.0).astype(dt)

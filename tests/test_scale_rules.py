@@ -20,7 +20,7 @@ def lib(tmp_path_factory):
     L = ctypes.CDLL(str(out))
     I, Lg = ctypes.c_int, ctypes.c_long
     L.t_direct_hold.argtypes = [Lg, I]
-    L.t_direct_rule.argtypes = [Lg, I, Lg, I, Lg, Lg]
+    L.t_direct_rule.argtypes = [Lg, I, Lg, I, Lg, Lg, Lg]
     L.t_row_cpt.argtypes = [I, I]
     L.t_scans_together.argtypes = [ctypes.POINTER(Lg)] * 2
     return L
@@ -38,25 +38,38 @@ def test_held_entries_follow_the_row(lib):
     assert lib.t_direct_hold(1025, 0) == 0
 
 
-# entry bytes, Cauchy-Schwarz rule, k, two sources, row-mode rows, columns
-DIRECT = [(16, 1, 200, 0, 96, 80), (16, 0, 777, 0, 500, 333), (16, 1, 1024, 0, 1024, 1024), (8, 0, 2051, 0, 1537, 1283),
-          (16, 1, 16, 0, 16384, 1), (16, 0, 16, 0, 24576, 0), (8, 1, 64, 0, 65536, 8192), (16, 1, 64, 0, 32, 65536),
-          (8, 0, 16384, 0, 4, 0), (16, 1, 64, 1, 4096, 0), (16, 0, 64, 1, 16384, 0), (8, 0, 0, 0, 5, 7)]
-SCANS = [(16, 1, 16, 0, 262144, 32), (16, 0, 16, 0, 262144, 32), (8, 1, 16, 0, 262144, 32), (8, 1, 64, 0, 65536, 32),
-         (16, 1, 8, 0, 65536, 2048), (8, 0, 32, 0, 65536, 64), (16, 1, 64, 1, 8192, 0), (8, 1, 64, 1, 16384, 0),
-         (8, 0, 0, 0, 1 << 27, 1), (16, 1, 16385, 0, 4, 4), (16, 0, 8193, 1, 4, 0), (16, 0, 2048, 0, 2048, 2048)]
+# entry bytes, Cauchy-Schwarz rule, k, two sources, rows of A and of B that are
+# rows of a column-major matrix, columns
+DIRECT = [(16, 1, 200, 0, 96, 0, 80), (16, 0, 777, 0, 500, 0, 333), (16, 1, 1024, 0, 1024, 0, 1024),
+          (8, 0, 2051, 0, 1537, 1283, 0), (16, 1, 16, 0, 16384, 0, 1), (16, 0, 16, 0, 24576, 0, 0),
+          (8, 1, 64, 0, 65536, 0, 8192), (16, 1, 64, 0, 32, 0, 65536), (8, 0, 16384, 0, 4, 0, 0),
+          (16, 1, 64, 1, 4096, 0, 0), (16, 0, 64, 1, 16384, 0, 0), (8, 0, 0, 0, 5, 0, 7),
+          (16, 1, 16, 0, 131072, 0, 8192), (8, 1, 1024, 0, 8000, 0, 0), (8, 1, 4000, 0, 1000, 0, 1000),
+          (8, 1, 4000, 0, 1000, 1000, 0), (8, 0, 8000, 0, 600, 0, 0), (16, 1, 16384, 0, 64, 0, 64),
+          (8, 1, 3584, 0, 0, 0, 1600), (8, 0, 16384, 0, 0, 0, 64), (8, 1, 5500, 1, 500, 0, 0)]
+SCANS = [(16, 1, 16, 0, 262144, 0, 32), (16, 0, 16, 0, 262144, 0, 32), (8, 1, 16, 0, 262144, 0, 32),
+         (8, 1, 64, 0, 65536, 0, 32), (16, 1, 8, 0, 65536, 0, 2048), (8, 0, 32, 0, 65536, 0, 64),
+         (16, 1, 64, 1, 8192, 0, 0), (8, 1, 64, 1, 16384, 0, 0), (8, 0, 0, 0, 1 << 27, 0, 1), (16, 1, 16385, 0, 4, 0, 4),
+         (16, 0, 8193, 1, 4, 0, 0), (16, 0, 2048, 0, 2048, 0, 2048), (8, 1, 8000, 0, 600, 0, 0),
+         (8, 1, 3000, 0, 0, 1500, 8), (16, 1, 4100, 0, 1100, 0, 8), (8, 1, 5500, 1, 800, 0, 0), (8, 1, 1100, 0, 8000, 0, 0),
+         (16, 1, 3585, 0, 0, 0, 2), (8, 1, 16384, 0, 0, 0, 128)]
+
+
+def direct(lib, e, cs, k, two, ra, rb, cols):
+    return lib.t_direct_rule(e, cs, k, two, ra + rb, max(ra, rb), cols)
 
 
 @pytest.mark.parametrize("case", DIRECT)
 def test_direct_calls(lib, case):
-    assert lib.t_direct_rule(*case) == 1
+    assert direct(lib, *case) == 1
 
 
 @pytest.mark.parametrize("case", SCANS)
 def test_scanned_calls(lib, case):
     """Many short rows (a wave each in the direct kernel, a lane in the row
-    scans), long rows, operands beyond the caches."""
-    assert lib.t_direct_rule(*case) == 0
+    scans), long rows, operands beyond the caches; under the Cauchy-Schwarz
+    rule large operands read in rows, and long columns."""
+    assert direct(lib, *case) == 0
 
 
 MB = 1 << 20
@@ -80,12 +93,12 @@ def test_scans_of_two_operands(lib, a, b, want):
 def test_sizes_of_the_scan_tests(lib, call, m, n, k, ta, tb, cpt, nt):
     """The GPU tests of the scans reach them, in the form they name."""
     e = 16 if call == "z" else 8
-    rows = (m if ta == "N" else 0) + (n if tb != "N" else 0)
-    assert lib.t_direct_rule(e, 1, k, 0, rows, m + n - rows) == 0
+    ra, rb = (m if ta == "N" else 0), (n if tb != "N" else 0)
+    assert direct(lib, e, 1, k, 0, ra, rb, m + n - ra - rb) == 0
     assert (lib.t_row_cpt(m, k) if ta == "N" else 0) == cpt
     assert (e * m * k >= 128 << 20) == nt
 
 
 def test_sizes_of_the_resummed_tests(lib):
-    assert lib.t_direct_rule(8, 1, RESUMMED_K, 0, 1, 0) == 0
-    assert lib.t_direct_rule(8, 1, RESUMMED_K_RANK2, 1, 1, 0) == 0
+    assert direct(lib, 8, 1, RESUMMED_K, 0, 1, 0, 0) == 0
+    assert direct(lib, 8, 1, RESUMMED_K_RANK2, 1, 1, 0, 0) == 0
