@@ -49,6 +49,17 @@
 // 8192 x 200 x 4096 248 against 255.  Past that k spread is the faster one
 // (4096 x 250 x 8192 243 against 228, 2500 x 200 x 30000 785 against 650),
 // which the plan does not use.
+//
+// Nor are launches of short k and few tiles spread (kept_flat): there is hardly
+// an operand strip to share, the launch is the writing of its outputs, and that
+// is faster with every product's rows and columns spread over the XCDs than
+// with whole products on one (GEMM phase flat against spread: 1000 x 1000 x 64
+// of 16 products 15.7 and 18.6 us, of 32 18.2 and 20.5, 1000 x 1000 x 256 of 16
+// 16.1 and 18.8, 700 x 700 x 192 of 16 12.1 and 14.9, 1600 x 1600 x 64 of 8 14.1
+// and 18.6, 600 x 2400 x 64 of 16 16.0 and 17.8; of longer k 1000 x 1000 x 384 of
+// 16 18.3 and 18.0, 1000 x 1000 x 256 of 32, two rounds, 27.4 and 24.7; of more
+// tiles 3000 x 3000 x 64 of 16 52.4 and 50.0; of panels 1000 x 300 x 256 of 16
+// 12.2 and 11.5, 4000 x 100 x 256 of 32 16.8 and 15.9).
 #pragma once
 
 #ifndef O2M_HD
@@ -198,11 +209,26 @@ struct GemmPlan {
 constexpr int kResident = 32;    // workgroups per XCD
 constexpr int kChainMin = 5, kChainMax = 48;
 
+// Launches that are not spread for their short k: up to two k-stages with at
+// most three tiles for each place on the chip, up to four with one, of four
+// tile-rows and tile-columns or more, where the XCD with the most tiles takes
+// no more rounds for it (36 tiles of 40 products, 128 x 128: 200 tiles on an XCD
+// of 96 places against 180, 18.6 us against 17.1 spread); 64 x 64 tiles are
+// level or up to 10% faster spread (200 x 200 x 256 of 32 products 8.0 and 8.9).
+O2M_HD inline bool kept_flat(const GemmShape &sh, int mt, int nt, int kblocks, int batch) {
+    const long rounds = kblocks <= 2 ? 3 : kblocks <= 4 ? 1 : 0, tiles = (long)mt * nt;
+    if (sh.tm < 128 || mt < 4 || nt < 4 || tiles * batch > rounds * kCus * sh.per_cu) return false;
+    const long places = kCus / kXcds * sh.per_cu;
+    const long flat = (tiles + kXcds - 1) / kXcds * batch, even = (tiles * batch + kXcds - 1) / kXcds;
+    return (flat + places - 1) / places == (even + places - 1) / places;
+}
+
 // rows x cols outputs per product, kblocks k-stages of stage_bytes per
 // 256-row operand tile, batch products.  A 256 x 256 launch is spread below 8
 // windows per product (a single tile-row or tile-column: below one tile per
 // XCD) and follows gemm_schedule otherwise; the smaller tiles, of which an XCD
-// holds per_cu windows, are spread below 8 of these and never pooled.
+// holds per_cu windows, are spread below 8 of these and never pooled; kept_flat
+// excepts some.
 O2M_HD inline GemmPlan gemm_plan(int rows, int cols, int kblocks, int batch, long stage_bytes) {
     GemmPlan p = {0, 0, 0, 0, 0, 0, {0, 0, 0, 0, 0}};
     if (rows <= 0 || cols <= 0 || batch <= 0 || kblocks <= 0) return p;
@@ -222,7 +248,8 @@ O2M_HD inline GemmPlan gemm_plan(int rows, int cols, int kblocks, int batch, lon
     p.nt = (cols - 1) / sh.tn + 1;
     const long tiles = (long)p.mt * p.nt;
     const bool narrow = p.shape == 0 && (p.mt == 1 || p.nt == 1);
-    const bool spread = tiles < (narrow ? kXcds : (long)kXcds * kWindowTiles * sh.per_cu);
+    const bool spread = tiles < (narrow ? kXcds : (long)kXcds * kWindowTiles * sh.per_cu) &&
+                        !kept_flat(sh, p.mt, p.nt, kblocks, batch);
     if (!spread && p.shape == 0) {
         p.s = gemm_schedule(p.mt, p.nt, kblocks, batch, stage_bytes);
     } else {

@@ -68,6 +68,28 @@ def test_plan_covers_every_tile_once(lib, rows, cols, kb, batch):
         assert slots == -(-mt * nt * batch // 8) and (np.diff(keys[:, 0]) >= 0).all()
 
 
+# rows, columns, k-stages, products of short launches; whether they are laid out spread
+SHORT = [(1000, 1000, 1, 16, False), (1000, 1000, 4, 16, False), (1000, 1000, 5, 16, True), (1000, 1000, 4, 32, True),
+         (1000, 1000, 2, 32, False), (700, 700, 4, 16, False), (1600, 1600, 2, 8, False), (2000, 2000, 2, 8, False),
+         (2000, 2000, 1, 16, True), (1025, 300, 1, 32, True), (300, 1025, 1, 32, True), (400, 400, 4, 16, False),
+         (200, 200, 4, 32, True), (700, 700, 2, 40, True), (700, 700, 2, 32, False),
+         (841, 835, 4, 8, False), (690, 655, 4, 16, False), (850, 780, 4, 16, False)]
+
+
+@pytest.mark.parametrize("rows,cols,kb,batch,spread", SHORT)
+def test_short_launches_are_kept_flat(lib, rows, cols, kb, batch, spread):
+    """Whichever layout, every tile has one slot."""
+    p = plan(lib, rows, cols, kb, batch)
+    assert (p["deal"] == 2) == spread
+    mt, nt, slots = p["mt"], p["nt"], p["slots"]
+    t = np.zeros((8, slots, 4), dtype=np.int32)
+    lib.t_plan_tiles(mt, nt, p["chunk"], p["deal"], batch, slots, t.ctypes.data)
+    keys = t[t[..., 0].astype(bool)][:, 1:].astype(np.int64)
+    flat = (keys[:, 0] * mt + keys[:, 1]) * nt + keys[:, 2]
+    assert (keys < [batch, mt, nt]).all() and len(flat) == len(np.unique(flat)) == mt * nt * batch
+    assert p["grid"] == 8 * slots and p["fixed"] == slots
+
+
 def test_empty_problem(lib):
     for c in [(0, 4, 4, 4), (4, 0, 4, 4), (4, 4, 0, 4), (4, 4, 4, 0)]:
         assert plan(lib, *c)["grid"] == 0
