@@ -105,8 +105,14 @@ template <int D> constexpr int per_thread() { return D == 1 ? 16 : 8; }
 // residue phase 14.1 us whole, 13.0 in two parts, 13.9 in four, 16.3 in eight;
 // 96 x 80 x 200, 160 waves: 12.1 whole, 7.5 in eight), above, the entries read
 // again cost more than the split gives (700^3, 2112 waves: 14.8 whole, 15.7 in
-// two parts).
-constexpr long kResidueWaves = 2048;
+// two parts).  With one digit and 16 entries per lane a wave does twice the
+// work of a launch of twice as many, and registers hold three to a SIMD: 768
+// (residue phase whole and in two parts: ZHERK 1088 x 1600 N = 10, 1700 waves,
+// 15.6 and 21.4 us, 600 x 1200, 722 waves, 11.4 and 11.5, in four 14.0; ZGEMM
+// 600 x 600 x 1300 N = 10, 1596 waves, 16.1 and 19.0; Gauss 666 x 666 x 1400
+// 10.4 and 12.5; ZHERK 500 x 1000, 512 waves, 12.4 whole, 10.2 in two parts, 11.1
+// in four).
+constexpr long kResidueWaves = 2048, kResidueWavesWhole = 768;
 constexpr int kMinModuli = 2;
 
 // PT residue bytes of one lane, contiguous in the plane (16- or 8-byte store).
@@ -405,9 +411,10 @@ hipError_t launch_residues(ElemType et, bool split, int count, const ResidueSour
     memset(&a, 0, sizeof a);
     for (int i = 0; i < count; ++i) a.src[i] = src[i];
     a.blocks0 = (unsigned)((waves[0] + 3) / 4);
-    // moduli per workgroup: split until the launch has kResidueWaves waves
+    // moduli per workgroup: split until the launch has that many waves
+    const long target = digits == 1 ? kResidueWavesWhole : kResidueWaves;
     a.mchunk = rp.n;
-    while (a.mchunk > kMinModuli && blocks * 4 * ((rp.n + a.mchunk - 1) / a.mchunk) < kResidueWaves)
+    while (a.mchunk > kMinModuli && blocks * 4 * ((rp.n + a.mchunk - 1) / a.mchunk) < target)
         a.mchunk = (a.mchunk + 1) / 2;
     a.rp = rp;
     const dim3 grid((unsigned)blocks, (unsigned)((rp.n + a.mchunk - 1) / a.mchunk));

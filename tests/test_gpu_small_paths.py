@@ -46,8 +46,8 @@ def op_of(x, t):
 # ------------------------------------------------------------------ residues
 # Fragments are 16 rows x 64 k: sizes one below, at and one above both; one
 # fragment row with padding beside it; the moduli split in parts (fewer than
-# 2048 waves) at odd counts, with a hybrid set cut inside its 2M and 3M moduli;
-# the two operands' digit counts apart (N = 13, k = 65 and N = 26, k = 17: two
+# 2048 waves, 768 with one digit) at odd counts, with a hybrid set cut inside
+# its 2M and 3M moduli; the two operands' digit counts apart (N = 13, k = 65 and N = 26, k = 17: two
 # launches); fp32 pairs with an odd row or k at the edge, and no pairs (odd
 # leading dimension); clamped indices must not read the NaN beyond the operand.
 RESIDUES = [
@@ -64,6 +64,8 @@ RESIDUES = [
     ("c", 33, 15, 63, 8, "cs", "T", "T", 1),
     ("c", 31, 47, 127, 5, "max", "N", "C", 2),
     ("c", 16, 48, 66, 8, "max", "C", "N", 2),
+    ("z", 120, 9, 3900, 5, "max", "N", "N", 0),     # one digit, rows up to 64-row tiles: 732 waves,
+    ("z", 140, 9, 3900, 5, "max", "N", "T", 1),     # and 976
 ]
 
 
