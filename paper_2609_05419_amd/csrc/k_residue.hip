@@ -97,7 +97,10 @@ __device__ inline uint32_t pack4(uint32_t b0, uint32_t b1, uint32_t b2, uint32_t
 // 159 -> 155, 8192^3 level; three digits 3000^3 N = 20 239 -> 221.  With one
 // digit (fp32 operands) 16 entries read whole lines with fewer loads: 8 took
 // 36 us instead of 30 for CGEMM 1537 x 1283 x 2051.
-template <int D> constexpr int per_thread() { return D == 1 ? 16 : 8; }
+// The split form loads two real entries for one (SYRK, DSYR2K), and 16 of those
+// spilled 24 registers: 8 as well (DSYRK 1200 x 3400 N = 10 20.6 -> 17.2 us, 800 x
+// 2400 14.4 -> 12.2, 4096^2 N = 4 46.7 -> 44.3, 3000 x 5000 N = 10 53.3 -> 51.2).
+template <int D, bool SPLIT> constexpr int per_thread() { return D == 1 && !SPLIT ? 16 : 8; }
 
 // The split of the moduli (mchunk): waves that a launch is brought to, and
 // moduli that a wave keeps at least.  2048 waves are two per SIMD; below, the
@@ -163,7 +166,7 @@ struct ResidueArgs {
 
 template <ElemType ET, int D, bool SCALED, bool PAIRS, bool SPLIT>
 __global__ __launch_bounds__(256, D == 1 ? 3 : 1) void residue_kernel(ResidueArgs a) {
-    constexpr int PT = per_thread<D>();
+    constexpr int PT = per_thread<D, SPLIT>();
     constexpr int kHalves = 16 / PT;                          // waves per fragment
     const ResidueParams &rp = a.rp;
     // what the loads need is read of both sources at once and then selected:
@@ -401,10 +404,11 @@ hipError_t launch_residues(ElemType et, bool split, int count, const ResidueSour
         const hipError_t e = launch_residues(et, split, 1, src, rp, st);
         return e != hipSuccess ? e : launch_residues(et, split, 1, src + 1, rp, st);
     }
-    // waves: one per fragment, two from two digits on (per_thread)
+    // waves: one per fragment of 16 entries a lane, two of 8 (per_thread)
+    const bool whole = digits == 1 && !split;
     long waves[2] = {0, 0};
     for (int i = 0; i < count; ++i)
-        waves[i] = (long)(src[i].g.rows_pad / kFragRows) * (long)src[i].g.kblocks * (digits == 1 ? 1 : 2);
+        waves[i] = (long)(src[i].g.rows_pad / kFragRows) * (long)src[i].g.kblocks * (whole ? 1 : 2);
     const long blocks = (waves[0] + 3) / 4 + (waves[1] + 3) / 4;
     if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
     ResidueArgs a;

@@ -80,7 +80,8 @@ def test_residue_edges(o2m, case):
     assert same_bits(got, ref(op_of(a, ta), op_of(b, tb), N, scaling=rule))
 
 
-@pytest.mark.parametrize("n,k,N,rule", [(17, 64, 16, "max"), (16, 63, 11, "cs"), (31, 129, 18, "max"), (1, 1, 16, "cs")])
+@pytest.mark.parametrize("n,k,N,rule", [(17, 64, 16, "max"), (16, 63, 11, "cs"), (31, 129, 18, "max"), (1, 1, 16, "cs"),
+                                        (33, 131, 5, "max"), (15, 255, 9, "cs")])
 def test_residue_edges_symmetric(o2m, n, k, N, rule):
     """Rank-2k sources in one launch, and the real split with odd k (its
     imaginary half ends one column before its k does)."""
