@@ -209,6 +209,15 @@ struct GemmPlan {
 constexpr int kResident = 32;    // workgroups per XCD
 constexpr int kChainMin = 5, kChainMax = 48;
 
+// One k-stage is the writing of the outputs, which the estimate does not know.
+// Long outputs, of up to 16 tile-rows or tile-columns of 128, are written faster
+// in 256 x 128 tiles than in 128 x 128 ones: 1000 x 30000 of 32 products 309 us
+// against 340, 2000 x 20000 424, 447, 20000 x 2000 368, 415, of 52 products 634,
+// 730, 1500 x 20000 317, 321; the others not (5000 x 5000 250, 232, 3000 x 10000 of
+// 16 147, 142), nor with two stages (500 x 30000 x 128 199, 195), nor where 256
+// rows pad an odd few tile-rows of 128 (300 x 60000 321, 260).
+constexpr int kLongTiles = 16;
+
 // Launches that are not spread for their short k: up to two k-stages with at
 // most three tiles for each place on the chip, up to four with one, of four
 // tile-rows and tile-columns or more, where the XCD with the most tiles takes
@@ -240,6 +249,12 @@ O2M_HD inline GemmPlan gemm_plan(int rows, int cols, int kblocks, int batch, lon
             best = t;
             p.shape = i;
         }
+    }
+    if (p.shape == 2 && kblocks == 1) {
+        const GemmShape s2 = gemm_shape_of(2);
+        const long r = ((long)rows - 1) / s2.tm + 1, c = ((long)cols - 1) / s2.tn + 1;
+        if (r * c >= kXcds * kWindowTiles * s2.per_cu && (r < c ? r : c) <= kLongTiles && (r % 2 == 0 || r >= kLongTiles))
+            p.shape = 1;
     }
     const GemmShape sh = gemm_shape_of(p.shape);
     p.tm = sh.tm;

@@ -90,6 +90,20 @@ def test_short_launches_are_kept_flat(lib, rows, cols, kb, batch, spread):
     assert p["grid"] == 8 * slots and p["fixed"] == slots
 
 
+# rows, columns, k-stages, products of long outputs; their tile shape
+LONG = [(2000, 20000, 1, 32, 1), (30000, 1000, 1, 16, 1), (2049, 20000, 1, 32, 2), (5000, 5000, 1, 32, 2),
+        (2000, 20000, 2, 32, 2), (2048, 6145, 1, 32, 1), (2048, 6016, 1, 32, 2),
+        (300, 60000, 1, 32, 2), (60000, 300, 1, 32, 1)]
+
+
+@pytest.mark.parametrize("rows,cols,kb,batch,shape", LONG)
+def test_long_outputs_of_one_stage(lib, rows, cols, kb, batch, shape):
+    p = plan(lib, rows, cols, kb, batch)
+    assert p["shape"] == shape and p["fixed"] == p["slots"] and p["grid"] == 8 * p["slots"]
+    assert (p["mt"] - 1) * p["tm"] < rows <= p["mt"] * p["tm"] and (p["nt"] - 1) * p["tn"] < cols <= p["nt"] * p["tn"]
+    assert p["slots"] * 8 >= p["mt"] * p["nt"] * batch
+
+
 def test_empty_problem(lib):
     for c in [(0, 4, 4, 4), (4, 0, 4, 4), (4, 4, 0, 4), (4, 4, 4, 0)]:
         assert plan(lib, *c)["grid"] == 0
